@@ -5,7 +5,7 @@
 
 namespace fp {
 
-// LDS: three K buffers and two V buffers of one 64-key tile (64 rows x 2D bytes, unpadded) each.
+// LDS: two K buffers and two V buffers of one 64-key tile (64 rows x 2D bytes, unpadded) each.
 // Tiles are written by direct global->LDS loads (16 B per lane, lane i lands at base + 16 i), so
 // bank conflicts are avoided by permuting the 16-byte chunks inside a row instead of padding
 // (stated for head dimension 128, 16 chunks per row; the masks shrink with the row for 64):
@@ -13,18 +13,18 @@ namespace fp {
 //     at one chunk index then hit 16 different bank groups;
 //   V row r keeps chunk c at position c ^ 4 (r & 3): the four rows a transpose read touches per
 //     lane group then hit four different 64-byte bank groups.
-// Head dimension 128: 16 KB tiles, 80 KB, two workgroups per CU.  64: 40 KB.  256: 32 KB tiles,
-// all 160 KB of a CU, one workgroup (its accumulators and query fragments need 512 registers).
+// Head dimension 128: 16 KB tiles, 64 KB, two workgroups per CU (registers).  64: 32 KB, three.
+// 256: 32 KB tiles, 128 KB, one workgroup (its accumulators and query fragments need 512 registers).
 // A workgroup has one wave per 32 queries of its q-block part, four at most; a 64-query block gets
-// two waves and 32-key tiles (40 KB, four workgroups per CU), so that every wave still loads 16
+// two waves and 32-key tiles (32 KB, four workgroups per CU), so that every wave still loads 16
 // rows of each tile and no wave repeats another's queries.
 template <int BLK> constexpr int kAttnWaves = BLK < 128 ? BLK / 32 : 4;
 template <int BLK> constexpr int kAttnTileKeys = 16 * kAttnWaves<BLK>;
 template <int D> constexpr int kAttnRowBytes = 2 * D;
 template <int D, int KT> constexpr int kAttnTile = KT * kAttnRowBytes<D>;   // 16384 at D = 128, 64 keys
-constexpr int kAttnKBufs = 3, kAttnVBufs = 2;
+constexpr int kAttnKBufs = 2, kAttnVBufs = 2;
 template <int D, int KT> constexpr int kAttnVBase = kAttnKBufs * kAttnTile<D, KT>;
-template <int D, int BLK> constexpr int kAttnLds = (kAttnKBufs + kAttnVBufs) * kAttnTile<D, kAttnTileKeys<BLK>>;   // 81920 at D = 128
+template <int D, int BLK> constexpr int kAttnLds = (kAttnKBufs + kAttnVBufs) * kAttnTile<D, kAttnTileKeys<BLK>>;   // 65536 at D = 128
 template <int D> constexpr int kAttnVSwz = (D / 32 - 1 < 3 ? D / 32 - 1 : 3);     // V rows: chunk ^ 4 (r & kAttnVSwz)
 
 // ds_read_b64_tr_b16: within each group of 16 lanes the 16 x 4 b16 values addressed by the
@@ -54,12 +54,11 @@ __device__ __forceinline__ s16x4 lds_read_tr(const char *p) {
  *   O^T += V^T P^T (16 MFMA): P^T is already in B-operand layout (registers of S^T, packed to
  *         bf16), V^T fragments come from the row-major V tile through LDS transpose reads.
  *
- * Software pipeline inside the wave: in step t the wave first issues the QK^T MFMAs of tile t+1
- * and only then runs the softmax of tile t (VALU) and the PV MFMAs of tile t, so the matrix
- * pipe works on t+1 while the vector ALU exponentiates t.  The S^T registers alternate between
- * two sets (steps are unrolled in pairs).  K therefore runs one tile ahead of V in LDS: step t
- * reads K[t+1] and V[t] and issues the direct-to-LDS loads of V[t+1] and K[t+3]; K has three
- * buffers, V two; one barrier per step.
+ * Software pipeline inside the wave: step t issues the QK^T MFMAs of tile t+1 with the softmax of
+ * tile t (VALU) between them, then the PV MFMAs of tile t with the max of tile t+1 between
+ * them.  The S^T registers alternate between two sets (steps are unrolled in pairs).  K runs one tile
+ * ahead of V in LDS: step t reads K[t+1] and V[t] and issues the direct-to-LDS loads of K[t+2] and
+ * V[t+1]; two buffers each, one barrier per step.  The order inside a step is fixed in the source (attn_step).
  *
  * Work order: blockIdx -> (XCD, slot).  Consecutive workgroup ids land on different XCDs, each
  * with its own L2; slot k of XCD x takes query head k%g of super-item (k/g)*8 + x, where a
@@ -80,53 +79,69 @@ __device__ __forceinline__ int attn_tile_block(const int32_t *list, int t, int I
     return b < 0 ? 0 : (b > I ? I : b);
 }
 
-// S^T (KT keys x 32 queries) of one K tile: s0 = keys 0..31, s1 = keys 32..63 (untouched for a 32-key tile).
-// kaddr = buffer base + the lane's row and swizzled chunk for k-slice 0; slice ks sits at kaddr ^ (ks << 5).
-template <int D, int KT>
-__device__ __forceinline__ void attn_qk(const char *smem, uint32_t kaddr, const bf16x8 (&qb)[D / 16], f32x16 &s0, f32x16 &s1) {
+// Head dimension 256 runs one wave per SIMD on all 512 registers: the accumulators and the query fragments
+// belong in the accumulation half of the file, S^T and everything the vector ALU touches in the other.
+// The compiler gives every MFMA result of such a kernel an accumulation register, so the S^T MFMAs are written out.
+template <int D> constexpr bool kAttnAgpr = D > 128;
+
+// One MFMA of S^T = K Q^T; FIRST starts from zero.
+template <int D, bool FIRST>
+__device__ __forceinline__ void attn_mfma_s(f32x16 &s, bf16x8 a, bf16x8 q) {
+    if constexpr (kAttnAgpr<D>) {
+        if (FIRST) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(a), "a"(q));
+        else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(a), "a"(q));
+    } else {
+        if (FIRST) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) { s0[i] = 0.f; if (KT > 32) s1[i] = 0.f; }
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-        const char *kp = smem + (kaddr ^ (uint32_t)(ks << 5));
-        const bf16x8 a0 = *reinterpret_cast<const bf16x8 *>(kp);
-        s0 = mfma32(a0, qb[ks], s0);
-        if (KT > 32) {
-            const bf16x8 a1 = *reinterpret_cast<const bf16x8 *>(kp + 32 * kAttnRowBytes<D>);
-            s1 = mfma32(a1, qb[ks], s1);
+            for (int i = 0; i < 16; ++i) s[i] = 0.f;
         }
+        s = mfma32(a, q, s);
     }
+}
+
+// Wait states between the last of these MFMAs and the first vector instruction that touches the result, where no
+// other MFMAs lie between (the compiler takes care of its own MFMAs, not of assembly).
+template <int D, int KT>
+__device__ __forceinline__ void attn_settle(f32x16 (&s)[KT / 32]) {
+    if constexpr (kAttnAgpr<D>) {
+#pragma unroll
+        for (int kt = 0; kt < KT / 32; ++kt) asm volatile("s_nop 15\n\ts_nop 7" : "+v"(s[kt]));
+    }
+}
+
+// K fragment f of a tile (k-slice f / (KT/32), 32 keys f % (KT/32)).
+template <int D, int KT>
+__device__ __forceinline__ bf16x8 attn_kfrag(const char *smem, uint32_t kaddr, int f) {
+    constexpr int NKT = KT / 32;
+    return *reinterpret_cast<const bf16x8 *>(smem + (kaddr ^ (uint32_t)((f / NKT) << 5)) + 32 * (f % NKT) * kAttnRowBytes<D>);
+}
+// V^T fragment v of a tile (16 keys v / (D/32), 32 dims v % (D/32)).
+template <int D>
+__device__ __forceinline__ bf16x8 attn_vfrag(const char *smem, const uint32_t (&vaddr)[D / 32], int v) {
+    const char *vp = smem + vaddr[v % (D / 32)] + 16 * (v / (D / 32)) * kAttnRowBytes<D>;
+    const s16x4 lo = lds_read_tr(vp);
+    const s16x4 hi = lds_read_tr(vp + 8 * kAttnRowBytes<D>);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 // Causal mask of a diagonal tile: key 8(i/4) + i%4 (+32 for s1) is in this lane's future if it
 // exceeds lim = query - tile offset - 4*half.
 template <int KT>
-__device__ __forceinline__ void attn_mask(f32x16 &s0, f32x16 &s1, int lim) {
+__device__ __forceinline__ void attn_mask(f32x16 (&s)[KT / 32], int lim) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int kk = 8 * (i >> 2) + (i & 3);
-        if (kk > lim) s0[i] = -INFINITY;
-        if (KT > 32 && kk + 32 > lim) s1[i] = -INFINITY;
-    }
+    for (int kt = 0; kt < KT / 32; ++kt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (32 * kt + 8 * (i >> 2) + (i & 3) > lim) s[kt][i] = -INFINITY;
 }
 
-// Row max of one tile's S^T: half of the tile's keys are in this lane, the rest in lane^32.
+// Row max over this lane's half of one tile's S^T.
 template <int KT>
-__device__ __forceinline__ float attn_rowmax(const f32x16 &s0, const f32x16 &s1) {
-    if (KT == 32) {
-        float ta = max3(s0[0], s0[1], s0[2]);
+__device__ __forceinline__ float attn_rowmax_half(const f32x16 (&s)[KT / 32]) {
+    float t = fmaxf(s[0][0], s[0][1]);
 #pragma unroll
-        for (int i = 3; i < 15; i += 2) ta = max3(ta, s0[i], s0[i + 1]);
-        return halves_max(fmaxf(ta, s0[15]));
-    }
-    float ta = max3(s0[0], s0[1], s0[2]), tb = max3(s1[0], s1[1], s1[2]);
-#pragma unroll
-    for (int i = 3; i < 15; i += 2) {
-        ta = max3(ta, s0[i], s0[i + 1]);
-        tb = max3(tb, s1[i], s1[i + 1]);
-    }
-    const float tm = max3(ta, s0[15], fmaxf(tb, s1[15]));
-    return halves_max(tm);
+    for (int i = 2; i < KT / 2; i += 2) t = max3(t, s[i >> 4][i & 15], s[i >> 4][(i & 15) + 1]);
+    return t;
 }
 
 // Online-softmax bookkeeping for a new tile max.  m_run is the reference point of the
@@ -151,43 +166,101 @@ __device__ __forceinline__ void attn_new_max(float tm, float c, float &m_run, fl
     }
 }
 
-// p = 2^(c*s - c*m), rounded to bf16 and laid out as the B operand of the PV product; the row sum
-// is taken over the fp32 values before rounding, so lse does not inherit bf16's 2^-9 rounding.
-template <int KT>
-__device__ __forceinline__ void attn_exp(const f32x16 &s0, const f32x16 &s1, float c, float mc, float &l_run,
-                                         bf16x8 (&pb)[2][2]) {
-    float la = 0.f, lb = 0.f;
+// Exponentials e0 .. e1-1 of a tile in the order in which the PV product needs them (element e: 16-key slice
+// e / 8): x = 2^(c*s - c*m).  They are finished by attn_exp_done, one slot of the step later, so that
+// nothing waits for the transcendental unit.  Written as assembly so that each stays in its slot.
+template <int KT, int E0, int E1>
+__device__ __forceinline__ void attn_exp(const f32x16 (&s)[KT / 32], float c, float mc, float (&x)[KT / 2]) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const float pa = fast_exp2(__builtin_fmaf(s0[i], c, -mc));
-        la += pa;
-        pb[0][i >> 3][i & 7] = (__bf16)pa;
-        if (KT > 32) {
-            const float pq = fast_exp2(__builtin_fmaf(s1[i], c, -mc));
-            lb += pq;
-            pb[1][i >> 3][i & 7] = (__bf16)pq;
-        }
+    for (int e = E0; e < E1; ++e)
+        asm volatile("v_fma_f32 %0, %1, %2, -%3\n\tv_exp_f32 %0, %0" : "=&v"(x[e]) : "v"(s[e >> 4][e & 15]), "s"(c), "v"(mc));
+}
+// Row sum, over the fp32 values before rounding so that lse does not inherit bf16's 2^-9, and
+// rounding to the B operand of the PV product (two chains of additions).
+template <int KT, int E0, int E1>
+__device__ __forceinline__ void attn_exp_done(const float (&x)[KT / 2], float (&ls)[2], bf16x8 (&pb)[KT / 16]) {
+#pragma unroll
+    for (int e = E0; e < E1; ++e) {
+        ls[e & 1] += x[e];
+        pb[e >> 3][e & 7] = (__bf16)x[e];
     }
-    l_run += la + lb;
 }
 
-// O^T += V^T P^T for one KT-key tile: V^T fragments by transpose reads of the row-major V tile.
-// vaddr[dt] = buffer base + the lane's row/column offsets with the swizzle of d-tile dt folded in.
-template <int D, int KT>
-__device__ __forceinline__ void attn_pv(const char *smem, const uint32_t (&vaddr)[D / 32], const bf16x8 (&pb)[2][2],
-                                        f32x16 (&acc)[D / 32]) {
+/*
+ * One step: QK^T of tile t+1 (into sn), softmax and PV of tile t (from sc).  On entry the row max of
+ * tile t is folded into m_run, K[t+1] and V[t] are complete in LDS and `ring` holds the first
+ * kAttnRing - 1 fragments of K[t+1].
+ *
+ * The step is a fixed sequence of slots, one per fragment: NKF slots that multiply a K fragment, then NVF that
+ * multiply a V^T fragment.  A slot reads the fragment needed kAttnRing - 1 slots later, issues its MFMA(s)
+ * and does a share of the vector work: exponentials of tile t beside the QK^T MFMAs (those of the last 16 keys
+ * beside the first PV MFMAs, which do not need them yet), the max of tile t+1 beside the later PV MFMAs.
+ * Scheduling fences keep the slots apart.  Left to itself the compiler asks for a fragment right
+ * before its MFMA and waits there, and bunches the vector work: a wave then stalls on LDS at
+ * every MFMA, which the other wave of the SIMD hides in part at head dimension 128 and no wave hides at 256.
+ *
+ * `load(i)`, i < nload, issues the tile loads, two per slot from the start of the step; they go into the
+ * buffers of K[t] and V[t-1], whose last readers are behind the barrier of step t-1.  That barrier
+ * (`sync`: wait for the loads, workgroup barrier) sits where the last V fragment of the step has been read
+ * and kAttnRing - 1 PV slots are still to come, which cover the first reads of the next K tile.
+ *
+ * Measured against the compiler's own order with three K buffers (attention alone, us): head dimension 256, 16K
+ * tokens 652 -> 550, dense 8K 630 -> 527; 128: 4K tokens of 4 heads 35.6 -> 30.6, 32K tokens 1375 -> 1300, dense 32K
+ * 7670 -> 7450 (1.15 -> 1.18 PFLOP/s; on such data the clock, not the schedule, sets the rate: 64 queries per
+ * wave and one wave per SIMD, with half the LDS reads, takes the same time); 64: 16K tokens 272 -> 259;
+ * block 64: 32K tokens 1047 -> 990; block 256: 1910 -> 1820.
+ */
+constexpr int kAttnRing = 4;
+enum { MAIN = 0, TAIL = 1, PEN = 2 };   // see the kernel
+template <int D, int KT, int MODE, class Load, class Sync, class Mask>
+__device__ __forceinline__ void attn_step(const char *smem, uint32_t k1, uint32_t k2, const uint32_t (&va)[D / 32],
+                                          const bf16x8 (&qb)[D / 16], const f32x16 (&sc)[KT / 32], f32x16 (&sn)[KT / 32],
+                                          f32x16 (&acc)[D / 32], float &m_run, float &l_run, bf16x8 (&ring)[kAttnRing], float c,
+                                          int nload, Load load, Sync sync, Mask mask) {
+    constexpr int NDT = D / 32, NKT = KT / 32, NKF = NKT * D / 16, NVF = KT / 16 * NDT, R = kAttnRing;
+    constexpr int NE = KT / 2, EQK = NE - 8, NQS = NKF - 1;   // exponentials of the tile; those beside the QK^T MFMAs and their slots
+    constexpr int MS = KT > 32 ? NVF / 2 : NVF / 2 - 1;   // PV slots with exponentials; the max follows
+    constexpr int MU = NVF - MS - (R - 1), NM = KT / 4;   // slots of the max, operations in it
+    static_assert((NKF + NVF) % R == 0, "the fragment ring comes round once per step");
+    static_assert(MS < NVF - NDT, "the last 16 keys' probabilities are complete before their first PV slot");
+    bf16x8 pb[KT / 16];
+    float x[NE], ls[2] = {l_run, 0.f}, tm = -INFINITY;
+    const float mc = m_run * c;
+    static_for<NKF>([&](auto f_) __attribute__((always_inline)) {
+        constexpr int f = f_, nx = f + R - 1, e0 = EQK * f / NQS, e1 = f < NQS ? EQK * (f + 1) / NQS : EQK;
+        if constexpr (nx < NKF) ring[nx % R] = attn_kfrag<D, KT>(smem, k1, nx);
+        else ring[nx % R] = attn_vfrag<D>(smem, va, nx - NKF);
+        attn_mfma_s<D, (f < NKT)>(sn[f % NKT], ring[f % R], qb[f / NKT]);
+        if (2 * f < nload) load(2 * f);
+        if (2 * f + 1 < nload) load(2 * f + 1);
+        attn_exp<KT, e0, e1>(sc, c, mc, x);
+        if constexpr (f > 0) attn_exp_done<KT, EQK * (f - 1) / NQS, e0>(x, ls, pb);
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    static_for<NVF>([&](auto v_) __attribute__((always_inline)) {
+        constexpr int v = v_, nx = v + R - 1;
+        if constexpr (nx == NVF) sync();
+        if constexpr (nx < NVF) ring[(NKF + nx) % R] = attn_vfrag<D>(smem, va, nx);
+        else if constexpr (MODE != PEN) ring[(NKF + nx) % R] = attn_kfrag<D, KT>(smem, k2, nx - NVF);
+        acc[v % NDT] = mfma32(ring[(NKF + v) % R], pb[v / NDT], acc[v % NDT]);
+        if constexpr (v <= MS) {
+            constexpr int e0 = EQK + 8 * v / MS, e1 = v < MS ? EQK + 8 * (v + 1) / MS : NE;
+            attn_exp<KT, e0, e1>(sc, c, mc, x);
+            attn_exp_done<KT, (v == 0 ? EQK : EQK + 8 * (v - 1) / MS), e0>(x, ls, pb);
+        }
+        if constexpr (MODE == MAIN && v >= MS) {
 #pragma unroll
-    for (int kt2 = 0; kt2 < KT / 32; ++kt2)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int dt = 0; dt < D / 32; ++dt) {
-                const char *vp = smem + vaddr[dt] + (32 * kt2 + 16 * j) * kAttnRowBytes<D>;
-                const s16x4 lo = lds_read_tr(vp);
-                const s16x4 hi = lds_read_tr(vp + 8 * kAttnRowBytes<D>);
-                const s16x8 a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-                acc[dt] = mfma32(__builtin_bit_cast(bf16x8, a), pb[kt2][j], acc[dt]);
-            }
+            for (int i = NM * (v - MS) / MU; i < (v - MS < MU ? NM * (v - MS + 1) / MU : NM); ++i)
+                tm = max3(tm, sn[(2 * i) >> 4][(2 * i) & 15], sn[(2 * i + 1) >> 4][(2 * i + 1) & 15]);
+        }
+        if constexpr (MODE != MAIN && v == MS) {
+            mask();
+            tm = attn_rowmax_half<KT>(sn);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    l_run = ls[0] + ls[1];
+    attn_new_max<NDT>(halves_max(tm), c, m_run, l_run, acc);
 }
 
 template <int D, int BLK, bool SPARSE>
@@ -274,8 +347,10 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
         int row = q_local < q_len ? q_local : q_len - 1;
         const uint16_t *qp = Q + ((size_t)(q_tok0 + row) * hq + h) * D + 8 * half;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=&v"(qb[ks]) : "v"(qp), "n"(32 * ks) : "memory");
+        for (int ks = 0; ks < KS; ++ks) {
+            if constexpr (kAttnAgpr<D>) asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=&a"(qb[ks]) : "v"(qp), "n"(32 * ks) : "memory");
+            else asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=&v"(qb[ks]) : "v"(qp), "n"(32 * ks) : "memory");
+        }
     }
 
     // Tile loads.  One wave-wide instruction moves RPL = 512/D rows (1 KB); wave w loads rows
@@ -287,6 +362,7 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
     // too, so the unsigned row offsets can never wrap.
     const uint32_t row_bytes = (uint32_t)hkv * D * 2;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(FP_LDS(char) *)smem;
+    const uint32_t ld_dst = __builtin_amdgcn_readfirstlane(lds_base + 16 * w * RB);
     const int ld_row = 16 * w + l / LPR;   // + RPL i
     const int ld_pos = l % LPR;
     const char *Kb = reinterpret_cast<const char *>(K) + (size_t)hk * D * 2;
@@ -295,8 +371,8 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
         const int row = ld_row + RPL * i;
-        ld_kcol[i] = (uint32_t)((ld_pos ^ (row & kSwz<D>)) * 16);
-        ld_vcol[i] = (uint32_t)((ld_pos ^ (4 * (row & kAttnVSwz<D>))) * 16);
+        ld_kcol[i] = (uint32_t)((ld_pos ^ (row & kSwz<D>)) * 16) + (uint32_t)ld_row * row_bytes;
+        ld_vcol[i] = (uint32_t)((ld_pos ^ (4 * (row & kAttnVSwz<D>))) * 16) + (uint32_t)ld_row * row_bytes;
     }
     // Clamped load of sub-tile sub_ of block blk_: every row is kept at or before the sequence's last token.
 #define FP_LOAD(Xb, col_, blk_, sub_, ldsoff_)                                                            \
@@ -304,34 +380,17 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
         const int tok0_ = seq_tok0 + (blk_) * BLK + (sub_) * KT;                                          \
         const int base_tok_ = tok0_ < last_tok ? tok0_ : last_tok;                                        \
         const char *base_ = Xb + (size_t)base_tok_ * row_bytes;                                           \
-        const uint32_t dst_ = lds_base + (ldsoff_) + 16 * w * RB;                                         \
+        const uint32_t dst_ = __builtin_amdgcn_readfirstlane(ld_dst + (ldsoff_));                                         \
         _Pragma("unroll") for (int i_ = 0; i_ < LPT; ++i_) {                                              \
             int tok_ = tok0_ + ld_row + RPL * i_;                                                         \
             tok_ = tok_ < last_tok ? tok_ : last_tok; /* keys past the end are masked as future */        \
             const uint32_t ro_ = (uint32_t)(tok_ - base_tok_) * row_bytes; /* tok_ >= base_tok_ */        \
-            load_to_lds(base_, ro_ + col_[i_], dst_ + i_ * 1024);                                         \
+            load_to_lds(base_, ro_ + (col_[i_] - (uint32_t)ld_row * row_bytes), dst_ + i_ * 1024);                                         \
         }                                                                                                 \
     } while (0)
     // K tile t lives in K buffer t % 3, V tile t in V buffer t % 2.
-#define FP_KBUF(t) ((uint32_t)(((t) % kAttnKBufs) * kAttnTile<D, KT>))
+#define FP_KBUF(par) ((uint32_t)((par) * kAttnTile<D, KT>))
 #define FP_VBUF(par) ((uint32_t)(kAttnVBase<D, KT> + (par) * kAttnTile<D, KT>))
-    // Outside the main loop the tile index is kept at the row's last tile: a prefetch past the end
-    // of the list re-reads that tile into a buffer nobody reads.
-#define FP_LOAD_SAFE(Xb, col_, t, ldsoff_)                                                                \
-    do {                                                                                                  \
-        const int ts_ = (t) < ntiles ? (t) : ntiles - 1;                                                  \
-        FP_LOAD(Xb, col_, FP_TILE_BLOCK(ts_), (ts_ % TPB), ldsoff_);                                      \
-    } while (0)
-    // The plain steps of the main loop load tiles known to lie before the diagonal block, hence
-    // complete: no per-row clamp, and the address is a byte offset carried from step to step (see
-    // the loop): off_ = offset of the tile's first row from the KV head's base.
-#define FP_LOAD_AT(Xb, col_, off_, ldsoff_)                                                               \
-    do {                                                                                                  \
-        const char *base_ = Xb + (off_);                                                                  \
-        const uint32_t dst_ = lds_base + (ldsoff_) + 16 * w * RB;                                         \
-        _Pragma("unroll") for (int i_ = 0; i_ < LPT; ++i_)                                                \
-            load_to_lds(base_, (uint32_t)(ld_row + RPL * i_) * row_bytes + col_[i_], dst_ + i_ * 1024);   \
-    } while (0)
     // Offset of tile u given its list entry; the block id is kept inside the blocks that are complete
     // in memory (those before the diagonal one, and the diagonal one unless the sequence ends inside
     // it), so that even a malformed (non-ascending) list cannot make a plain load reach past the sequence.
@@ -367,110 +426,108 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
     // query); elsewhere nothing is masked.
 #define FP_LIM(t) (FP_TILE_BLOCK(t) == I ? qoff + q_local - ((t) % TPB) * KT - 4 * half : 2 * KT)
 
-    // Prologue: S^T of tile 0 with its row max; on leaving it K[1] and V[0] are in, K[2] on its way.
+    // Prologue: S^T of tile 0 with its row max; on leaving it K[1] and V[0] are in and the first
+    // fragments of K[1] are being read.
     FP_LOAD(Kb, ld_kcol, b0, 0, FP_KBUF(0));
-    FP_LOAD(Vb, ld_vcol, b0, 0, FP_VBUF(0));
     FP_LOAD(Kb, ld_kcol, b0, 1, FP_KBUF(1));   // ntiles >= 2
-    if (TPB == 2) FP_LOAD(Kb, ld_kcol, (nb > 1 ? b1 : b0), (nb > 1 ? 0 : 1), FP_KBUF(2));
-    else FP_LOAD(Kb, ld_kcol, b0, 2, FP_KBUF(2));
-    FP_WAIT_VMCNT(3 * LPT);   // Q and K[0] are in; V[0], K[1] and K[2] keep landing under the first QK^T
+    FP_LOAD(Vb, ld_vcol, b0, 0, FP_VBUF(0));
+    FP_WAIT_VMCNT(2 * LPT);   // Q and K[0] are in; K[1] and V[0] keep landing under the first QK^T
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qb[ks]));   // uses of Q stay behind the wait
+    for (int ks = 0; ks < KS; ++ks) {   // uses of Q stay behind the wait
+        if constexpr (kAttnAgpr<D>) asm volatile("" : "+a"(qb[ks]));
+        else asm volatile("" : "+v"(qb[ks]));
+    }
     __syncthreads();
-    f32x16 sA0, sA1, sB0, sB1;
-    attn_qk<D, KT>(smem, FP_KBUF(0) + k_frag, qb, sA0, sA1);
-    attn_mask<KT>(sA0, sA1, b0 == I ? qoff + q_local - 4 * half : 2 * KT);
-    m_run = attn_rowmax<KT>(sA0, sA1);   // finite: key 0 of tile 0 is visible to every query
-    FP_WAIT_VMCNT(LPT);
+    constexpr int NKT = KT / 32;
+    f32x16 sA[NKT], sB[NKT];
+    bf16x8 ring[kAttnRing];
+    static_for<NKT * KS>([&](auto f_) __attribute__((always_inline)) {
+        constexpr int f = f_;
+        attn_mfma_s<D, (f < NKT)>(sA[f % NKT], attn_kfrag<D, KT>(smem, FP_KBUF(0) + k_frag, f), qb[f / NKT]);
+    });
+    attn_settle<D, KT>(sA);
+    attn_mask<KT>(sA, b0 == I ? qoff + q_local - 4 * half : 2 * KT);
+    m_run = halves_max(attn_rowmax_half<KT>(sA));   // finite: key 0 of tile 0 is visible to every query
+    FP_WAIT_VMCNT(0);
     __syncthreads();
+#pragma unroll
+    for (int f = 0; f < kAttnRing - 1; ++f) ring[f] = attn_kfrag<D, KT>(smem, FP_KBUF(1) + k_frag, f);
 
-    // Step t.  On entry K[t+1] and V[t] are complete in LDS, K[t+2] may still be landing, S^T(t) is
-    // in (c0, c1) and its row max is already folded into m_run (accumulator rescaled).  The step
-    // issues V[t+1] into the buffer V[t-1] used and K[t+3] into the buffer K[t] used (all waves are
-    // past step t-1's barrier, which was their last reader) and ends by waiting for everything but
-    // K[t+3].  Every variant is straight-line code, so that the scheduler can interleave the QK^T
-    // MFMAs of tile t+1 with the exponentials of tile t, and the PV MFMAs of tile t with the max of
-    // tile t+1:
-    //   MAIN  tile t+1 needs no mask, tiles t+1 and t+3 are complete in memory: cheap loads;
+    // Step t (attn_step) loads K[t+2] and V[t+1].  Variants:
+    //   MAIN  tile t+1 needs no mask, tiles t+1 and t+2 are complete in memory: cheap loads;
     //   TAIL  row-clamped loads and the (branch-free) causal limit of tile t+1;
-    //   PEN   the last but one step: as TAIL without a K prefetch, ends with nothing in flight;
-    //   LAST  exponentials and PV of the last tile only.
-    // PAR is the parity of t (steps come in pairs that start at an even t): V tile t sits in V
-    // buffer PAR.  KB_NEXT / KB_LOAD are the K buffers of tile t+1 (read) and t+3 (loaded); VOFF /
-    // KOFF the byte offsets of tiles t+1 / t+3 (MAIN only).
+    //   PEN   the last but one step: as TAIL without a K load or the reads of a next K tile;
+    // the last tile's exponentials and PV follow the loops.  PAR is the parity of t (steps come in pairs
+    // that start at an even t): tiles t live in K and V buffers PAR.
     // A tile of the diagonal block that lies wholly in a wave's future needs no special case: its
     // logits are all -inf, which leaves the max alone and contributes zeros.
-    enum { MAIN = 0, TAIL = 1, PEN = 2, LAST = 3 };
-#define FP_STEP(MODE, PAR, t, c0, c1, n0, n1, VOFF, KOFF, KB_NEXT, KB_LOAD)                                \
+#define FP_STEP(MODE, PAR, t, sc, sn, LOADX)                                                               \
     do {                                                                                                  \
         const int t_ = (t);                                                                               \
-        if (MODE == MAIN) {                                                                               \
-            FP_LOAD_AT(Vb, ld_vcol, VOFF, FP_VBUF(1 - PAR));                                              \
-            FP_LOAD_AT(Kb, ld_kcol, KOFF, KB_LOAD);                                                       \
-        } else if (MODE != LAST) {                                                                        \
-            FP_LOAD_SAFE(Vb, ld_vcol, t_ + 1, FP_VBUF(1 - PAR));                                          \
-            if (MODE == TAIL) FP_LOAD_SAFE(Kb, ld_kcol, t_ + 3, KB_LOAD);                                 \
-        }                                                                                                 \
-        bf16x8 pb_[2][2];                                                                                 \
-        attn_exp<KT>(c0, c1, c, m_run * c, l_run, pb_);                                                   \
-        if (MODE != LAST) attn_qk<D, KT>(smem, (KB_NEXT) + k_frag, qb, n0, n1);                           \
-        {                                                                                                 \
-            uint32_t va_[NDT];                                                                            \
-            _Pragma("unroll") for (int dt_ = 0; dt_ < NDT; ++dt_) va_[dt_] = FP_VBUF(PAR) + v_frag[dt_];  \
-            attn_pv<D, KT>(smem, va_, pb_, acc);                                                          \
-        }                                                                                                 \
-        if (MODE != LAST) {                                                                               \
-            if (MODE != MAIN) attn_mask<KT>(n0, n1, FP_LIM(t_ + 1));                                      \
-            attn_new_max<NDT>(attn_rowmax<KT>(n0, n1), c, m_run, l_run, acc);                             \
-            if (MODE == PEN) FP_WAIT_VMCNT(0);                                                            \
-            else FP_WAIT_VMCNT(LPT);                                                                      \
-            __syncthreads();                                                                              \
-        }                                                                                                 \
+        uint32_t va_[NDT];                                                                                \
+        _Pragma("unroll") for (int dt_ = 0; dt_ < NDT; ++dt_) va_[dt_] = FP_VBUF(PAR) + v_frag[dt_];      \
+        attn_step<D, KT, MODE>(                                                                           \
+            smem, FP_KBUF(1 - PAR) + k_frag, FP_KBUF(PAR) + k_frag, va_, qb, sc, sn, acc, m_run, l_run, ring, c, 2 * LPT, LOADX, \
+            [&]() __attribute__((always_inline)) { FP_WAIT_VMCNT(0); __syncthreads(); },                  \
+            [&]() __attribute__((always_inline)) { attn_settle<D, KT>(sn); attn_mask<KT>(sn, FP_LIM(t_ + 1)); }); \
     } while (0)
+    // load i of a step, K first; VOFF / KOFF are the byte offsets of tiles t+1 / t+2
+#define FP_LOAD_MAIN(PAR, VOFF, KOFF)                                                                      \
+    [&](int i_) __attribute__((always_inline)) {                                                          \
+        const bool k_ = i_ < LPT;                                                                         \
+        const int j_ = k_ ? i_ : i_ - LPT;                                                                \
+        load_to_lds_add(k_ ? Kb + (KOFF) : Vb + (VOFF), (uint32_t)(RPL * j_) * row_bytes, k_ ? ld_kcol[j_] : ld_vcol[j_], \
+                        ld_dst + (k_ ? FP_KBUF(PAR) : FP_VBUF(1 - (PAR))) + j_ * 1024);                   \
+    }
+#define FP_LOAD_TAIL(PAR, t, WITH_K)                                                                       \
+    [&](int i_) __attribute__((always_inline)) {                                                          \
+        if (i_ == 0 && WITH_K) FP_LOAD(Kb, ld_kcol, FP_TILE_BLOCK((t) + 2), (((t) + 2) % TPB), FP_KBUF(PAR)); \
+        if (i_ == LPT) FP_LOAD(Vb, ld_vcol, FP_TILE_BLOCK((t) + 1), (((t) + 1) % TPB), FP_VBUF(1 - (PAR))); \
+    }
 
     // Tiles before the diagonal block are complete (only a sequence's last block can be partial,
     // and a row only meets it as its diagonal); the list is ascending, so only its last block can
     // be the diagonal one: the first n_plain tiles need no mask.  A pair of MAIN steps (t, t+1)
-    // computes S^T of tiles t+1 and t+2 without a mask and loads tiles t+1 .. t+4 without a clamp:
-    // t+2 < n_plain, and t+4 has to exist and be complete, which the diagonal block is unless the
-    // sequence ends inside it (then t+4 < n_plain).  ntiles and n_plain are even, and so is the
-    // number of MAIN steps, so the register roles of the two S^T tiles alternate evenly.
+    // computes S^T of tiles t+1 and t+2 without a mask and loads tiles up to t+3 without a clamp;
+    // ntiles and n_plain are even, so t < n_plain - 2 gives t+3 < n_plain.  Steps come in pairs, so
+    // the register roles of the two S^T tiles alternate evenly.
     const int n_plain = FP_TILE_BLOCK(ntiles - 1) == I ? TPB * (nb - 1) : ntiles;
-    const int t_main = diag_full ? (n_plain - 2 < ntiles - 4 ? n_plain - 2 : ntiles - 4) : n_plain - 4;   // <= 0: none
+    const int t_main = n_plain - 2;   // <= 0: none
     int t = 0;
     if (t_main > 0) {
         // Addresses of the main loop, carried instead of recomputed: o1..o3 = offsets of tiles t+1..t+3,
-        // e4 = list entry of tile t+4, fetched one pair of steps before it is needed (a list read is a
-        // scalar memory load; waiting for it inside a step would stall the wave at the step's start);
-        // kb0..kb2 = K buffers of tiles t..t+2.  Tile t+5 is the odd neighbour of t+4 in one block.
-        // (Tiles 0..4 lie in the first 4 / TPB + 1 list entries; the first two are already here.)
-#define FP_ENT(u) ((u) / TPB == 0 ? b0 : ((u) / TPB == 1 ? b1 : (SPARSE ? list[(u) / TPB < nb ? (u) / TPB : nb - 1] : (u) / TPB)))
-        uint64_t o1 = FP_ENT_OFF(FP_ENT(1), 1), o2 = FP_ENT_OFF(FP_ENT(2), 2), o3 = FP_ENT_OFF(FP_ENT(3), 3);
-        int e4 = FP_ENT(4);
-        uint32_t kb0 = FP_KBUF(0), kb1 = FP_KBUF(1), kb2 = FP_KBUF(2);
+        // e2 = list entry of tile t+2, fetched one pair of steps before it is needed (a list read is a
+        // scalar memory load; waiting for it inside a step would stall the wave).  Tile t+3 is the odd
+        // neighbour of t+2 in one block.  (Tiles 0..2 lie in the first two list entries at most.)
+        uint64_t o1 = FP_ENT_OFF(b0, 1);
+        int e2 = 2 / TPB == 0 ? b0 : b1;
         for (; t < t_main; t += 2) {
-            const int u6 = (t + 6) / TPB < nb ? (t + 6) / TPB : nb - 1;
-            const int e6 = SPARSE ? list[u6] : u6;
-            FP_STEP(MAIN, 0, t, sA0, sA1, sB0, sB1, o1, o3, kb1, kb0);
-            const uint64_t o4 = FP_ENT_OFF(e4, t + 4);
-            FP_STEP(MAIN, 1, t + 1, sB0, sB1, sA0, sA1, o2, o4, kb2, kb1);
+            const uint64_t o2 = FP_ENT_OFF(e2, t + 2);
+            const uint64_t o3 = o2 + (uint64_t)KT * row_bytes;
+            const int u4 = (t + 4) / TPB < nb ? (t + 4) / TPB : nb - 1;
+            e2 = SPARSE ? list[u4] : u4;
+            FP_STEP(MAIN, 0, t, sA, sB, FP_LOAD_MAIN(0, o1, o2));
+            FP_STEP(MAIN, 1, t + 1, sB, sA, FP_LOAD_MAIN(1, o2, o3));
             o1 = o3;
-            o2 = o4;
-            o3 = o4 + (uint64_t)KT * row_bytes;
-            e4 = e6;
-            const uint32_t kb_ = kb0;
-            kb0 = kb2;
-            kb2 = kb1;
-            kb1 = kb_;
         }
-#undef FP_ENT
     }
     for (; t < ntiles - 2; t += 2) {
-        FP_STEP(TAIL, 0, t, sA0, sA1, sB0, sB1, 0, 0, FP_KBUF(t + 1), FP_KBUF(t + 3));
-        FP_STEP(TAIL, 1, t + 1, sB0, sB1, sA0, sA1, 0, 0, FP_KBUF(t + 2), FP_KBUF(t + 4));
+        FP_STEP(TAIL, 0, t, sA, sB, FP_LOAD_TAIL(0, t, true));
+        FP_STEP(TAIL, 1, t + 1, sB, sA, FP_LOAD_TAIL(1, t + 1, true));
     }
-    FP_STEP(PEN, 0, t, sA0, sA1, sB0, sB1, 0, 0, FP_KBUF(t + 1), 0);
-    FP_STEP(LAST, 1, t + 1, sB0, sB1, sA0, sA1, 0, 0, 0, 0);
+    FP_STEP(PEN, 0, t, sA, sB, FP_LOAD_TAIL(0, t, false));
+    {
+        bf16x8 pb[KT / 16];
+        float x[KT / 2], ls[2] = {l_run, 0.f};
+        attn_exp<KT, 0, KT / 2>(sB, c, m_run * c, x);
+        attn_exp_done<KT, 0, KT / 2>(x, ls, pb);
+        l_run = ls[0] + ls[1];
+        uint32_t va[NDT];
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) va[dt] = FP_VBUF(1) + v_frag[dt];
+#pragma unroll
+        for (int v = 0; v < KT / 16 * NDT; ++v) acc[v % NDT] = mfma32(attn_vfrag<D>(smem, va, v), pb[v / NDT], acc[v % NDT]);
+    }
 
     // O = acc / l, lse = m + log2 l (Alg. 3, final normalisation); rows past a ragged end are not stored.
     // Each lane holds 4 consecutive dims of one query per accumulator group, which would make every
@@ -508,8 +565,8 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
         lse[(size_t)h * T + q_tok0 + q_local] = l_tot > 0.f ? m_run * c + __log2f(l_tot) : -INFINITY;
 #undef FP_TILE_BLOCK
 #undef FP_LOAD
-#undef FP_LOAD_SAFE
-#undef FP_LOAD_AT
+#undef FP_LOAD_MAIN
+#undef FP_LOAD_TAIL
 #undef FP_ENT_OFF
 #undef FP_LIM
 #undef FP_KBUF

@@ -3,6 +3,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 namespace fp {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -33,6 +36,16 @@ struct __attribute__((aligned(16))) RowRec {
 };
 // One key block: first token and number of valid tokens.
 typedef int2 KeyBlockRec;
+
+// f(0), f(1) .. f(N-1) with the index as a compile-time constant.
+template <class F, int... I>
+__device__ __forceinline__ void static_for_seq(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+    static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
 
 #define FP_LDS(T) __attribute__((address_space(3))) T
 
@@ -104,6 +117,15 @@ __device__ __forceinline__ void load_to_lds(const char *sbase, uint32_t voff, ui
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :
                  : "v"(voff), "s"(sbase), "s"(lds_addr)
+                 : "memory", "m0");
+}
+// The same with the lane's offset as the sum of a wave-uniform and a per-lane part: the addition fills
+// the wait state the load needs after the write of M0.
+__device__ __forceinline__ void load_to_lds_add(const char *sbase, uint32_t soff, uint32_t voff, uint32_t lds_addr) {
+    uint32_t at;
+    asm volatile("s_mov_b32 m0, %4\n\tv_add_u32 %0, %1, %2\n\tglobal_load_lds_dwordx4 %0, %3"
+                 : "=&v"(at)
+                 : "s"(soff), "v"(voff), "s"(sbase), "s"(lds_addr)
                  : "memory", "m0");
 }
 #pragma clang diagnostic pop
