@@ -30,12 +30,24 @@ __global__ __launch_bounds__(256) void pool_k_kernel(const uint16_t *__restrict_
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.f;
     const uint4 *base = reinterpret_cast<const uint4 *>(K);
-    for (int k = rg; k < bi.y; k += RG) {
-        const uint4 v = base[((size_t)(bi.x + k) * hkv + hk) * CPR + chunk];
-        acc[0] += bf16lo(v.x); acc[1] += bf16hi(v.x);
-        acc[2] += bf16lo(v.y); acc[3] += bf16hi(v.y);
-        acc[4] += bf16lo(v.z); acc[5] += bf16hi(v.z);
-        acc[6] += bf16lo(v.w); acc[7] += bf16hi(v.w);
+    // Eight loads per thread in flight (a whole 128-key block at D = 128): with one the kernel was eight
+    // round trips to memory long, which is what a short prompt waits for (1000 tokens, whole pass: 33.3 -> 31.4 us).
+    constexpr int NB = 128 / RG < 8 ? 128 / RG : 8;
+    for (int k0 = rg; k0 < bi.y; k0 += NB * RG) {
+        uint4 v[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int k = k0 + i * RG < bi.y ? k0 + i * RG : bi.y - 1;
+            v[i] = base[((size_t)(bi.x + k) * hkv + hk) * CPR + chunk];
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+            if (k0 + i * RG < bi.y) {
+                acc[0] += bf16lo(v[i].x); acc[1] += bf16hi(v[i].x);
+                acc[2] += bf16lo(v[i].y); acc[3] += bf16hi(v[i].y);
+                acc[4] += bf16lo(v[i].z); acc[5] += bf16hi(v[i].z);
+                acc[6] += bf16lo(v[i].w); acc[7] += bf16hi(v[i].w);
+            }
     }
 #pragma unroll
     for (int j = 0; j < 8; ++j) red[rg][chunk * 8 + j] = acc[j];
