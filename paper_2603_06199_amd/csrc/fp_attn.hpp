@@ -176,14 +176,20 @@ __device__ __forceinline__ void attn_exp(const f32x16 (&s)[KT / 32], float c, fl
         asm volatile("v_fma_f32 %0, %1, %2, -%3\n\tv_exp_f32 %0, %0" : "=&v"(x[e]) : "v"(s[e >> 4][e & 15]), "s"(c), "v"(mc));
 }
 // Row sum, over the fp32 values before rounding so that lse does not inherit bf16's 2^-9, and
-// rounding to the B operand of the PV product (two chains of additions).
+// rounding to the B operand of the PV product.  One chain of additions per 32 keys, started afresh in every
+// tile: a chain that went on from the running sum would round it once per key instead of once per tile.
 template <int KT, int E0, int E1>
-__device__ __forceinline__ void attn_exp_done(const float (&x)[KT / 2], float (&ls)[2], bf16x8 (&pb)[KT / 16]) {
+__device__ __forceinline__ void attn_exp_done(const float (&x)[KT / 2], float (&ls)[KT / 32], bf16x8 (&pb)[KT / 16]) {
 #pragma unroll
     for (int e = E0; e < E1; ++e) {
-        ls[e & 1] += x[e];
+        ls[e >> 4] += x[e];
         pb[e >> 3][e & 7] = (__bf16)x[e];
     }
+}
+template <int KT>
+__device__ __forceinline__ float attn_tile_sum(const float (&ls)[KT / 32]) {
+    if constexpr (KT > 32) return ls[0] + ls[1];
+    else return ls[0];
 }
 
 /*
@@ -224,7 +230,7 @@ __device__ __forceinline__ void attn_step(const char *smem, uint32_t k1, uint32_
     static_assert((NKF + NVF) % R == 0, "the fragment ring comes round once per step");
     static_assert(MS < NVF - NDT, "the last 16 keys' probabilities are complete before their first PV slot");
     bf16x8 pb[KT / 16];
-    float x[NE], ls[2] = {l_run, 0.f}, tm = -INFINITY;
+    float x[NE], ls[NKT] = {}, tm = -INFINITY;
     const float mc = m_run * c;
     static_for<NKF>([&](auto f_) __attribute__((always_inline)) {
         constexpr int f = f_, nx = f + R - 1, e0 = EQK * f / NQS, e1 = f < NQS ? EQK * (f + 1) / NQS : EQK;
@@ -259,7 +265,7 @@ __device__ __forceinline__ void attn_step(const char *smem, uint32_t k1, uint32_
         }
         __builtin_amdgcn_sched_barrier(0);
     });
-    l_run = ls[0] + ls[1];
+    l_run += attn_tile_sum<KT>(ls);
     attn_new_max<NDT>(halves_max(tm), c, m_run, l_run, acc);
 }
 
@@ -518,10 +524,10 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
     FP_STEP(PEN, 0, t, sA, sB, FP_LOAD_TAIL(0, t, false));
     {
         bf16x8 pb[KT / 16];
-        float x[KT / 2], ls[2] = {l_run, 0.f};
+        float x[KT / 2], ls[NKT] = {};
         attn_exp<KT, 0, KT / 2>(sB, c, m_run * c, x);
         attn_exp_done<KT, 0, KT / 2>(x, ls, pb);
-        l_run = ls[0] + ls[1];
+        l_run += attn_tile_sum<KT>(ls);
         uint32_t va[NDT];
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) va[dt] = FP_VBUF(1) + v_frag[dt];
