@@ -166,15 +166,30 @@ __device__ __forceinline__ void attn_new_max(float tm, float c, float &m_run, fl
     }
 }
 
-// Exponentials e0 .. e1-1 of a tile in the order in which the PV product needs them (element e: 16-key slice
+// Exponentials E0 .. E1-1 of a tile in the order in which the PV product needs them (element e: 16-key slice
 // e / 8): x = 2^(c*s - c*m).  They are finished by attn_exp_done, one slot of the step later, so that
-// nothing waits for the transcendental unit.  Written as assembly so that each stays in its slot.
+// nothing waits for the transcendental unit.  Written as assembly so that each stays in its slot.  The compiler
+// does not see what is inside:
+//   - the result of v_exp_f32 needs one wait state before a vector instruction reads it: the next element's
+//     v_fma_f32 (after the last one a wait) stands behind it in the same statement;
+//   - the MFMA results in s need none here: mc follows from the row max of the whole tile (attn_new_max), so
+//     that instructions the compiler does see (at head dimension 256: attn_settle, or the PV MFMAs before
+//     the max) have waited for every element before.
+#define FP_FMA(x, s) "v_fma_f32 %[" x "], %[" s "], %[c], -%[mc]\n\t"
+#define FP_EXP "v_exp_f32 %[x], %[x]\n\t"
 template <int KT, int E0, int E1>
 __device__ __forceinline__ void attn_exp(const f32x16 (&s)[KT / 32], float c, float mc, float (&x)[KT / 2]) {
-#pragma unroll
-    for (int e = E0; e < E1; ++e)
-        asm volatile("v_fma_f32 %0, %1, %2, -%3\n\tv_exp_f32 %0, %0" : "=&v"(x[e]) : "v"(s[e >> 4][e & 15]), "s"(c), "v"(mc));
+    static_for<E1 - E0>([&](auto i_) __attribute__((always_inline)) {
+        constexpr int e = E0 + i_, n = e + 1 < KT / 2 ? e + 1 : e;
+        const float se = s[e >> 4][e & 15], sn = s[n >> 4][n & 15];
+        float &xe = x[e], &xn = x[n];
+        if constexpr (e == 0) asm volatile(FP_FMA("x", "s") FP_EXP FP_FMA("y", "t") : [x] "=&v"(xe), [y] "=&v"(xn) : [s] "v"(se), [t] "v"(sn), [c] "s"(c), [mc] "v"(mc));
+        else if constexpr (n > e) asm volatile(FP_EXP FP_FMA("y", "t") : [x] "+v"(xe), [y] "=&v"(xn) : [t] "v"(sn), [c] "s"(c), [mc] "v"(mc));
+        else asm volatile(FP_EXP "s_nop 0" : [x] "+v"(xe));
+    });
 }
+#undef FP_FMA
+#undef FP_EXP
 // Row sum, over the fp32 values before rounding so that lse does not inherit bf16's 2^-9, and
 // rounding to the B operand of the PV product.  One chain of additions per 32 keys, started afresh in every
 // tile: a chain that went on from the running sum would round it once per key instead of once per tile.
@@ -254,6 +269,7 @@ __device__ __forceinline__ void attn_step(const char *smem, uint32_t k1, uint32_
             attn_exp<KT, e0, e1>(sc, c, mc, x);
             attn_exp_done<KT, (v == 0 ? EQK : EQK + 8 * (v - 1) / MS), e0>(x, ls, pb);
         }
+        if constexpr (v == MS + 1) l_run += attn_tile_sum<KT>(ls);
         if constexpr (MODE == MAIN && v >= MS) {
 #pragma unroll
             for (int i = NM * (v - MS) / MU; i < (v - MS < MU ? NM * (v - MS + 1) / MU : NM); ++i)
@@ -265,7 +281,6 @@ __device__ __forceinline__ void attn_step(const char *smem, uint32_t k1, uint32_
         }
         __builtin_amdgcn_sched_barrier(0);
     });
-    l_run += attn_tile_sum<KT>(ls);
     attn_new_max<NDT>(halves_max(tm), c, m_run, l_run, acc);
 }
 
