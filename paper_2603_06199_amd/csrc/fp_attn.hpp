@@ -84,12 +84,14 @@ __device__ __forceinline__ int attn_tile_block(const int32_t *list, int t, int I
 // The compiler gives every MFMA result of such a kernel an accumulation register, so the S^T MFMAs are written out.
 template <int D> constexpr bool kAttnAgpr = D > 128;
 
-// One MFMA of S^T = K Q^T; FIRST starts from zero.
+// One MFMA of S^T = K Q^T; FIRST starts from zero.  An operand that a vector instruction wrote (a register copy: the
+// fragments come from loads) needs two wait states before the MFMA, which the compiler does not give to assembly.
+#define FP_MFMA(C) "v_mfma_f32_32x32x16_bf16 %[d], %[a], %[q], " C
 template <int D, bool FIRST>
 __device__ __forceinline__ void attn_mfma_s(f32x16 &s, bf16x8 a, bf16x8 q) {
     if constexpr (kAttnAgpr<D>) {
-        if (FIRST) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(a), "a"(q));
-        else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(a), "a"(q));
+        if constexpr (FIRST) asm volatile("s_nop 1\n\t" FP_MFMA("0") : [d] "=&v"(s) : [a] "v"(a), [q] "a"(q));
+        else asm volatile("s_nop 1\n\t" FP_MFMA("%[d]") : [d] "+v"(s) : [a] "v"(a), [q] "a"(q));
     } else {
         if (FIRST) {
 #pragma unroll
@@ -106,6 +108,16 @@ __device__ __forceinline__ void attn_settle(f32x16 (&s)[KT / 32]) {
     if constexpr (kAttnAgpr<D>) {
 #pragma unroll
         for (int kt = 0; kt < KT / 32; ++kt) asm volatile("s_nop 15\n\ts_nop 7" : "+v"(s[kt]));
+    }
+}
+
+// The same where N MFMAs of the compiler's lie between: only the reads of the result are held behind this point.
+template <int D, int KT, int N>
+__device__ __forceinline__ void attn_settled_by_pv(f32x16 (&s)[KT / 32]) {
+    if constexpr (kAttnAgpr<D>) {
+        static_assert(N >= 3, "8 wait states each, one after another: the third starts past the 20 a result needs at most");
+#pragma unroll
+        for (int kt = 0; kt < KT / 32; ++kt) asm volatile("" : "+v"(s[kt]));
     }
 }
 
@@ -188,8 +200,27 @@ __device__ __forceinline__ void attn_exp(const f32x16 (&s)[KT / 32], float c, fl
         else asm volatile(FP_EXP "s_nop 0" : [x] "+v"(xe));
     });
 }
+// Exponential E and one MFMA of S^T in one statement, for head dimension 256: the vector instructions are the MFMA's
+// wait states.
+template <int KT, bool FIRST, int E>
+__device__ __forceinline__ void attn_exp_mfma(f32x16 &d, bf16x8 a, bf16x8 q, const f32x16 (&s)[KT / 32], float c, float mc,
+                                              float (&x)[KT / 2]) {
+    static_assert(E + 1 < KT / 2 && (!FIRST || E == 0), "a tile starts with the first MFMAs of its S^T and ends beside the PV MFMAs");
+    const float se = s[E >> 4][E & 15], sn = s[(E + 1) >> 4][(E + 1) & 15];
+    float &xe = x[E], &xn = x[E + 1];
+    if constexpr (FIRST)
+        asm volatile(FP_FMA("x", "s") FP_EXP FP_FMA("y", "t") FP_MFMA("0")
+                     : [x] "=&v"(xe), [y] "=&v"(xn), [d] "=&v"(d) : [s] "v"(se), [t] "v"(sn), [c] "s"(c), [mc] "v"(mc), [a] "v"(a), [q] "a"(q));
+    else if constexpr (E == 0)
+        asm volatile(FP_FMA("x", "s") FP_EXP FP_FMA("y", "t") FP_MFMA("%[d]")
+                     : [x] "=&v"(xe), [y] "=&v"(xn), [d] "+v"(d) : [s] "v"(se), [t] "v"(sn), [c] "s"(c), [mc] "v"(mc), [a] "v"(a), [q] "a"(q));
+    else
+        asm volatile(FP_EXP FP_FMA("y", "t") FP_MFMA("%[d]")
+                     : [x] "+v"(xe), [y] "=&v"(xn), [d] "+v"(d) : [t] "v"(sn), [c] "s"(c), [mc] "v"(mc), [a] "v"(a), [q] "a"(q));
+}
 #undef FP_FMA
 #undef FP_EXP
+#undef FP_MFMA
 // Row sum, over the fp32 values before rounding so that lse does not inherit bf16's 2^-9, and
 // rounding to the B operand of the PV product.  One chain of additions per 32 keys, started afresh in every
 // tile: a chain that went on from the running sum would round it once per key instead of once per tile.
@@ -251,10 +282,12 @@ __device__ __forceinline__ void attn_step(const char *smem, uint32_t k1, uint32_
         constexpr int f = f_, nx = f + R - 1, e0 = EQK * f / NQS, e1 = f < NQS ? EQK * (f + 1) / NQS : EQK;
         if constexpr (nx < NKF) ring[nx % R] = attn_kfrag<D, KT>(smem, k1, nx);
         else ring[nx % R] = attn_vfrag<D>(smem, va, nx - NKF);
-        attn_mfma_s<D, (f < NKT)>(sn[f % NKT], ring[f % R], qb[f / NKT]);
+        if constexpr (kAttnAgpr<D> && e1 > e0) attn_exp_mfma<KT, (f < NKT), e0>(sn[f % NKT], ring[f % R], qb[f / NKT], sc, c, mc, x);
+        else attn_mfma_s<D, (f < NKT)>(sn[f % NKT], ring[f % R], qb[f / NKT]);
         if (2 * f < nload) load(2 * f);
         if (2 * f + 1 < nload) load(2 * f + 1);
-        attn_exp<KT, e0, e1>(sc, c, mc, x);
+        if constexpr (!kAttnAgpr<D>) attn_exp<KT, e0, e1>(sc, c, mc, x);
+        else static_assert(e1 - e0 <= 1, "attn_exp_mfma takes one exponential");
         if constexpr (f > 0) attn_exp_done<KT, EQK * (f - 1) / NQS, e0>(x, ls, pb);
         __builtin_amdgcn_sched_barrier(0);
     });
@@ -270,6 +303,7 @@ __device__ __forceinline__ void attn_step(const char *smem, uint32_t k1, uint32_
             attn_exp_done<KT, (v == 0 ? EQK : EQK + 8 * (v - 1) / MS), e0>(x, ls, pb);
         }
         if constexpr (v == MS + 1) l_run += attn_tile_sum<KT>(ls);
+        if constexpr (MODE == MAIN && v == MS) attn_settled_by_pv<D, KT, MS>(sn);
         if constexpr (MODE == MAIN && v >= MS) {
 #pragma unroll
             for (int i = NM * (v - MS) / MU; i < (v - MS < MU ? NM * (v - MS + 1) / MU : NM); ++i)

@@ -4,7 +4,8 @@ into no asm statement.  These rules are checked over every path through every at
 
   exponentials   a v_exp_f32 in a statement is followed in the same statement by an instruction that does not read
                  its result (one wait state before a vector instruction may)
-  mfma operands  a vector instruction that writes an operand of an MFMA in a statement lies two wait states before it
+  mfma operands  an MFMA in a statement has two wait states before it in the same statement, so that whatever wrote
+                 an operand is that old, and what the statement itself writes before it is no operand of it
   mfma results   nothing but another MFMA touches those of an MFMA in a statement for 20 wait states (what a
                  16-pass MFMA asks for; these have 8); no statement touches those of any other MFMA for as long
   query loads    nothing touches the registers of a load in a statement before the next wait for vmcnt
@@ -126,6 +127,12 @@ def test_exponentials(attention):
 def test_mfma_operands(attention):
     bad = []
     for k in attention:
+        for region in k.regions:
+            before = 0
+            for i in region:
+                if k.ins[i].mfma and before < 2:
+                    bad.append(f"{k.name}: {k.ins[i].text}: {before} wait states before it in its statement")
+                before += k.ins[i].states
         for i, p in enumerate(k.ins):
             if p.valu:
                 bad += [f"{k.name}: {p.text} -> {u.text}" for u in k.after(i, 2) if u.mfma and u.asm and u.reads & p.writes]
