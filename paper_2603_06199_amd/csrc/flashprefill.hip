@@ -330,8 +330,8 @@ template <int D, int BLK>
 static fp_status launch_search_d(fp_plan *p, const void *Q, const void *K, float eps, float *scores,
                                  const fp::SelectArgs *sel, hipStream_t st, uint16_t *kb_hi, uint16_t *kb_lo,
                                  float2 *kb_norm) {
-    fp::pool_k_kernel<D><<<dim3(p->kb_total, p->hkv), 256, 0, st>>>(static_cast<const uint16_t *>(K), p->d_kblk, p->hkv,
-                                                                     p->c, kb_hi, kb_lo, kb_norm);
+    fp::pool_k_kernel<D, BLK><<<dim3(p->kb_total, p->hkv), 256, 0, st>>>(static_cast<const uint16_t *>(K), p->d_kblk, p->hkv,
+                                                                          p->c, kb_hi, kb_lo, kb_norm);
     const int nchunk = (p->g + fp::kSearchHeads<BLK> - 1) / fp::kSearchHeads<BLK>;
     const dim3 grid(p->m_total * p->hkv * nchunk);
     const uint16_t *q = static_cast<const uint16_t *>(Q);

@@ -14,7 +14,7 @@ namespace fp {
 // Next to the planes go two norms per pooled key: |hi + lo|_2 (bounds every logit against it by
 // Cauchy-Schwarz) and |lo|_2 (bounds what a product with the hi plane alone leaves out).
 // ---------------------------------------------------------------------------------------------
-template <int D>
+template <int D, int BLK>
 __global__ __launch_bounds__(256) void pool_k_kernel(const uint16_t *__restrict__ K,
                                                      const KeyBlockRec *__restrict__ kblk, int hkv, float c,
                                                      uint16_t *__restrict__ kb_hi, uint16_t *__restrict__ kb_lo,
@@ -30,9 +30,10 @@ __global__ __launch_bounds__(256) void pool_k_kernel(const uint16_t *__restrict_
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.f;
     const uint4 *base = reinterpret_cast<const uint4 *>(K);
-    // Eight loads per thread in flight (a whole 128-key block at D = 128): with one the kernel was eight
-    // round trips to memory long, which is what a short prompt waits for (1000 tokens, whole pass: 33.3 -> 31.4 us).
-    constexpr int NB = 128 / RG < 8 ? 128 / RG : 8;
+    // Up to eight loads per thread in flight, no more than a whole block has rows for: 8 at D = 128 (a whole 128-key
+    // block, half of a 256-key one) and 256 (half a block), 4 at D = 64 and for a 64-key block.  With one the kernel was
+    // eight round trips to memory long, which is what a short prompt waits for (1000 tokens, whole pass: 33.3 -> 31.4 us).
+    constexpr int NB = BLK / RG < 8 ? BLK / RG : 8;
     for (int k0 = rg; k0 < bi.y; k0 += NB * RG) {
         uint4 v[NB];
 #pragma unroll

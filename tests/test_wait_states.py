@@ -187,3 +187,11 @@ def test_tile_loads(attention):
                         if u.asm and u.op.startswith("global_load") and u.reads & sgprs]
     _fail_if(bad)
     assert n > 100
+
+
+def test_pooled_key_loads(assembly):
+    """The pooling kernel has no more row loads in flight than a full key block has rows for its row groups."""
+    for d, block, loads in ((64, 128, 4), (128, 64, 4), (128, 128, 8), (128, 256, 8), (256, 128, 8)):
+        lines = [v for n, v in assembly.items() if f"pool_k_kernelILi{d}ELi{block}E" in n]
+        assert len(lines) == 1
+        assert sum("global_load_dwordx4" in line for line in lines[0]) == loads, (d, block)
