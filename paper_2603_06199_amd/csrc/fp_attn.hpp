@@ -136,7 +136,7 @@ __device__ __forceinline__ bf16x8 attn_vfrag(const char *smem, const uint32_t (&
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// Causal mask of a diagonal tile: key 8(i/4) + i%4 (+32 for s1) is in this lane's future if it
+// Causal mask of a diagonal tile: key 32 kt + 8(i/4) + i%4 (element i of s[kt]) is in this lane's future if it
 // exceeds lim = query - tile offset - 4*half.
 template <int KT>
 __device__ __forceinline__ void attn_mask(f32x16 (&s)[KT / 32], int lim) {
@@ -256,11 +256,11 @@ __device__ __forceinline__ float attn_tile_sum(const float (&ls)[KT / 32]) {
  * (`sync`: wait for the loads, workgroup barrier) sits where the last V fragment of the step has been read
  * and kAttnRing - 1 PV slots are still to come, which cover the first reads of the next K tile.
  *
- * Measured against the compiler's own order with three K buffers (attention alone, us): head dimension 256, 16K
- * tokens 652 -> 550, dense 8K 630 -> 527; 128: 4K tokens of 4 heads 35.6 -> 30.6, 32K tokens 1375 -> 1300, dense 32K
- * 7670 -> 7450 (1.15 -> 1.18 PFLOP/s; on such data the clock, not the schedule, sets the rate: 64 queries per
- * wave and one wave per SIMD, with half the LDS reads, takes the same time); 64: 16K tokens 272 -> 259;
- * block 64: 32K tokens 1047 -> 990; block 256: 1910 -> 1820.
+ * Measured against the compiler's own order with three K buffers (attention alone, launches back to back, both in turn
+ * on one card, us): head dimension 256, 16K tokens 654 -> 561, dense 8K 633 -> 547; 128: 4K tokens of 4 heads 35.3 -> 30.4,
+ * 32K tokens 1425 -> 1357, dense 32K 7992 -> 7801; 64: 16K tokens 275 -> 268; block 64: 32K tokens 1047 -> 997; block 256:
+ * 1994 -> 1897.  Long rows at head dimension 128 gain least because the clock sets most of their rate: on all-zero inputs
+ * the same launch of dense 32K takes 1 / 1.55 of the time (64: 1 / 1.34, 256: 1 / 1.20, 16K tokens).
  */
 constexpr int kAttnRing = 4;
 enum { MAIN = 0, TAIL = 1, PEN = 2 };   // see the kernel
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
             load_to_lds(base_, ro_ + (col_[i_] - (uint32_t)ld_row * row_bytes), dst_ + i_ * 1024);                                         \
         }                                                                                                 \
     } while (0)
-    // K tile t lives in K buffer t % 3, V tile t in V buffer t % 2.
+    // Tile t lives in K and V buffer t % 2.
 #define FP_KBUF(par) ((uint32_t)((par) * kAttnTile<D, KT>))
 #define FP_VBUF(par) ((uint32_t)(kAttnVBase<D, KT> + (par) * kAttnTile<D, KT>))
     // Offset of tile u given its list entry; the block id is kept inside the blocks that are complete

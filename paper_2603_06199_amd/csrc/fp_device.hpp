@@ -15,7 +15,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 // The kernels are templates over the head dimension D (64, 128 or 256).  A row of D bf16 is
 // D/8 16-byte chunks; LDS tiles are unpadded and keep chunk c of row r at position c ^ (r & kSwz<D>)
@@ -100,6 +99,8 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // becomes one v_max3_f32 instead of three canonicalising v_max_f32 plus the max itself.  It must
 // stay a compiler-visible instruction: the wait states the hardware needs between an MFMA and a
 // VALU read of its result are inserted by the compiler, and inline assembly would not get them.
+// (The attention kernel's exponentials are assembly and read MFMA results all the same: each of them has
+// gone through a max3 before.  Results of MFMAs that are themselves assembly get no wait states here either.)
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
 // 16 bytes per lane, global -> LDS, no register staging: lane i's 16 bytes, fetched from

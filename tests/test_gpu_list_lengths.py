@@ -1,8 +1,8 @@
 """GPU parity of the attention kernels over the length of a row's list.  A row runs its list as plain steps,
 masked steps and two closing steps, in pairs of tiles; which of them occur, and how often, depends on the
 number of listed blocks, on whether the diagonal block is among them and on whether the sequence ends
-inside it.  Lists of 0 .. 6 blocks with and without the diagonal one, on full and ragged last blocks,
-at every head dimension and block size, against the oracle."""
+inside it.  Lists of 0 .. 6 blocks with and without the diagonal one, and of all of a row's 1 .. 9 blocks, on full and
+ragged last blocks, at every head dimension and block size, against the oracle."""
 import numpy as np
 import pytest
 
