@@ -228,7 +228,7 @@ template <int KT, int E0, int E1>
 __device__ __forceinline__ void attn_exp_done(const float (&x)[KT / 2], float (&ls)[KT / 32], bf16x8 (&pb)[KT / 16]) {
 #pragma unroll
     for (int e = E0; e < E1; ++e) {
-        ls[e >> 4] += x[e];
+        ls[e >> 4] = (e & 15) ? ls[e >> 4] + x[e] : x[e];
         pb[e >> 3][e & 7] = (__bf16)x[e];
     }
 }
@@ -276,7 +276,7 @@ __device__ __forceinline__ void attn_step(const char *smem, uint32_t k1, uint32_
     static_assert((NKF + NVF) % R == 0, "the fragment ring comes round once per step");
     static_assert(MS < NVF - NDT, "the last 16 keys' probabilities are complete before their first PV slot");
     bf16x8 pb[KT / 16];
-    float x[NE], ls[NKT] = {}, tm = -INFINITY;
+    float x[NE], ls[NKT], tm = -INFINITY;
     const float mc = m_run * c;
     static_for<NKF>([&](auto f_) __attribute__((always_inline)) {
         constexpr int f = f_, nx = f + R - 1, e0 = EQK * f / NQS, e1 = f < NQS ? EQK * (f + 1) / NQS : EQK;
@@ -573,7 +573,7 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
     FP_STEP(PEN, 0, t, sA, sB, FP_LOAD_TAIL(0, t, false));
     {
         bf16x8 pb[KT / 16];
-        float x[KT / 2], ls[NKT] = {};
+        float x[KT / 2], ls[NKT];
         attn_exp<KT, 0, KT / 2>(sB, c, m_run * c, x);
         attn_exp_done<KT, 0, KT / 2>(x, ls, pb);
         l_run += attn_tile_sum<KT>(ls);
