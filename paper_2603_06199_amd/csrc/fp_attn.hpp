@@ -8,7 +8,8 @@ namespace fp {
 // LDS: two K buffers and two V buffers of one 64-key tile (64 rows x 2D bytes, unpadded) each.
 // Tiles are written by direct global->LDS loads (16 B per lane, lane i lands at base + 16 i), so
 // bank conflicts are avoided by permuting the 16-byte chunks inside a row instead of padding
-// (stated for head dimension 128, 16 chunks per row; the masks shrink with the row for 64):
+// (stated for head dimension 128, 16 chunks per row; the masks shrink with the row for 64, whose rows are half a turn
+// of the banks long: there K rows eight apart meet, and half of the LDS unit's active cycles are conflicts):
 //   K row r keeps chunk c at position c ^ (r & 15): the A-fragment reads of 16 consecutive rows
 //     at one chunk index then hit 16 different bank groups;
 //   V row r keeps chunk c at position c ^ 4 (r & 3): the four rows a transpose read touches per
