@@ -86,6 +86,10 @@ __device__ __forceinline__ int attn_tile_block(const int32_t *list, int t, int I
 // The compiler gives every MFMA result of such a kernel an accumulation register, so the S^T MFMAs are written out.
 template <int D> constexpr bool kAttnAgpr = D > 128;
 
+// Whether a lane's load offsets include the row of each load (one vector instruction less per load).  At head dimension 256,
+// with twice the loads per tile, the addition stays in the wait state of the load (16K tokens 2 % slower without it).
+template <int D> constexpr bool kAttnRowInOffset = D <= 128;
+
 // One MFMA of S^T = K Q^T; FIRST starts from zero.  An operand that a vector instruction wrote (a register copy: the
 // fragments come from loads) needs two wait states before the MFMA, which the compiler does not give to assembly.
 #define FP_MFMA(C) "v_mfma_f32_32x32x16_bf16 %[d], %[a], %[q], " C
@@ -250,8 +254,9 @@ __device__ __forceinline__ float attn_tile_sum(const float (&ls)[KT / 32]) {
  * kAttnRing - 1 fragments of K[t+1].
  *
  * The step is a fixed sequence of slots, one per fragment: NKF slots that multiply a K fragment, then NVF that
- * multiply a V^T fragment.  A slot reads the fragment needed kAttnRing - 1 slots later, issues its MFMA(s)
- * and does a share of the vector work: exponentials of tile t beside the QK^T MFMAs (those of the last 16 keys
+ * multiply a V^T fragment.  A slot issues its MFMA, reads the fragment needed kAttnRing - 1 slots later
+ * and does a share of the vector work (in this order: behind an MFMA a wave's next vector instruction waits for some
+ * 16 cycles, which the reads and the tile loads do not): exponentials of tile t beside the QK^T MFMAs (those of the last 16 keys
  * beside the first PV MFMAs, which do not need them yet), the max of tile t+1 beside the later PV MFMAs.
  * Scheduling fences keep the slots apart.  Left to itself the compiler asks for a fragment right
  * before its MFMA and waits there, and bunches the vector work: a wave then stalls on LDS at
@@ -286,12 +291,14 @@ __device__ __forceinline__ void attn_step(const char *smem, uint32_t k1, uint32_
     const float mc = m_run * c;
     static_for<NKF>([&](auto f_) __attribute__((always_inline)) {
         constexpr int f = f_, nx = f + R - 1, e0 = EQK * f / NQS, e1 = f < NQS ? EQK * (f + 1) / NQS : EQK;
-        if constexpr (nx < NKF) ring[nx % R] = attn_kfrag<D, KT>(smem, k1, nx);
-        else ring[nx % R] = attn_vfrag<D>(smem, va, nx - NKF);
         if constexpr (kAttnAgpr<D> && e1 > e0) attn_exp_mfma<KT, (f < NKT), e0>(sn[f % NKT], ring[f % R], qb[f / NKT], sc, c, mc, x);
         else attn_mfma_s<D, (f < NKT)>(sn[f % NKT], ring[f % R], qb[f / NKT]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (nx < NKF) ring[nx % R] = attn_kfrag<D, KT>(smem, k1, nx);
+        else ring[nx % R] = attn_vfrag<D>(smem, va, nx - NKF);
         if (2 * f < nload) load(2 * f);
         if (2 * f + 1 < nload) load(2 * f + 1);
+        __builtin_amdgcn_sched_barrier(0);
         if constexpr (!kAttnAgpr<D>) attn_exp<KT, e0, e1>(sc, c, mc, x);
         else static_assert(e1 - e0 <= 1, "attn_exp_mfma takes one exponential");
         if constexpr (f > 0) attn_exp_done<KT, EQK * (f - 1) / NQS, e0>(x, ls, pb);
@@ -300,9 +307,11 @@ __device__ __forceinline__ void attn_step(const char *smem, uint32_t k1, uint32_
     static_for<NVF>([&](auto v_) __attribute__((always_inline)) {
         constexpr int v = v_, nx = v + R - 1;
         if constexpr (nx == NVF) sync();
+        acc[v % NDT] = mfma32(ring[(NKF + v) % R], pb[v / NDT], acc[v % NDT]);
+        __builtin_amdgcn_sched_barrier(0);
         if constexpr (nx < NVF) ring[(NKF + nx) % R] = attn_vfrag<D>(smem, va, nx);
         else if constexpr (MODE != PEN) ring[(NKF + nx) % R] = attn_kfrag<D, KT>(smem, k2, nx - NVF);
-        acc[v % NDT] = mfma32(ring[(NKF + v) % R], pb[v / NDT], acc[v % NDT]);
+        __builtin_amdgcn_sched_barrier(0);
         if constexpr (v <= MS) {
             constexpr int e0 = EQK + 8 * v / MS, e1 = v < MS ? EQK + 8 * (v + 1) / MS : NE;
             attn_exp<KT, e0, e1>(sc, c, mc, x);
@@ -429,12 +438,12 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
     const int ld_pos = l % LPR;
     const char *Kb = reinterpret_cast<const char *>(K) + (size_t)hk * D * 2;
     const char *Vb = reinterpret_cast<const char *>(V) + (size_t)hk * D * 2;
-    uint32_t ld_kcol[LPT], ld_vcol[LPT];
+    uint32_t ld_kcol[LPT], ld_vcol[LPT];   // byte offset from the tile's first row; see kAttnRowInOffset
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
-        const int row = ld_row + RPL * i;
-        ld_kcol[i] = (uint32_t)((ld_pos ^ (row & kSwz<D>)) * 16) + (uint32_t)ld_row * row_bytes;
-        ld_vcol[i] = (uint32_t)((ld_pos ^ (4 * (row & kAttnVSwz<D>))) * 16) + (uint32_t)ld_row * row_bytes;
+        const int row = ld_row + RPL * i, off_row = kAttnRowInOffset<D> ? row : ld_row;
+        ld_kcol[i] = (uint32_t)((ld_pos ^ (row & kSwz<D>)) * 16) + (uint32_t)off_row * row_bytes;
+        ld_vcol[i] = (uint32_t)((ld_pos ^ (4 * (row & kAttnVSwz<D>))) * 16) + (uint32_t)off_row * row_bytes;
     }
     // Clamped load of sub-tile sub_ of block blk_: every row is kept at or before the sequence's last token.
 #define FP_LOAD(Xb, col_, blk_, sub_, ldsoff_)                                                            \
@@ -447,7 +456,7 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
             int tok_ = tok0_ + ld_row + RPL * i_;                                                         \
             tok_ = tok_ < last_tok ? tok_ : last_tok; /* keys past the end are masked as future */        \
             const uint32_t ro_ = (uint32_t)(tok_ - base_tok_) * row_bytes; /* tok_ >= base_tok_ */        \
-            load_to_lds(base_, ro_ + (col_[i_] - (uint32_t)ld_row * row_bytes), dst_ + i_ * 1024);                                         \
+            load_to_lds(base_, ro_ + (col_[i_] - (uint32_t)(ld_row + (kAttnRowInOffset<D> ? RPL * i_ : 0)) * row_bytes), dst_ + i_ * 1024); \
         }                                                                                                 \
     } while (0)
     // Tile t lives in K and V buffer t % 2.
@@ -538,8 +547,11 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
     [&](int i_) __attribute__((always_inline)) {                                                          \
         const bool k_ = i_ < LPT;                                                                         \
         const int j_ = k_ ? i_ : i_ - LPT;                                                                \
-        load_to_lds_add(k_ ? Kb + (KOFF) : Vb + (VOFF), (uint32_t)(RPL * j_) * row_bytes, k_ ? ld_kcol[j_] : ld_vcol[j_], \
-                        ld_dst + (k_ ? FP_KBUF(PAR) : FP_VBUF(1 - (PAR))) + j_ * 1024);                   \
+        const char *base_ = k_ ? Kb + (KOFF) : Vb + (VOFF);                                               \
+        const uint32_t col_ = k_ ? ld_kcol[j_] : ld_vcol[j_];                                             \
+        const uint32_t dst_ = ld_dst + (k_ ? FP_KBUF(PAR) : FP_VBUF(1 - (PAR))) + j_ * 1024;              \
+        if constexpr (kAttnRowInOffset<D>) load_to_lds(base_, col_, dst_);                                \
+        else load_to_lds_add(base_, (uint32_t)(RPL * j_) * row_bytes, col_, dst_);                        \
     }
 #define FP_LOAD_TAIL(PAR, t, WITH_K)                                                                       \
     [&](int i_) __attribute__((always_inline)) {                                                          \
