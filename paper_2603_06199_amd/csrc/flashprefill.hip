@@ -9,6 +9,7 @@
 #include <mutex>
 #include <new>
 #include <numeric>
+#include <type_traits>
 #include <vector>
 
 #include "fp_attn.hpp"
@@ -46,6 +47,8 @@ void *static_scratch(int device) {
 // (m, S) of one row for 2 heads must fit the score kernel's LDS next to its tile buffers
 // (2 x 16 KB + 1 KB + 2 x 8 B x blocks <= 160 KB would allow more; 4096 blocks = 512K tokens)
 constexpr int kMaxBlocksPerSeq = 4096;
+constexpr int kLdsPerWorkgroup = 160 * 1024;
+constexpr int kCus = 256;
 
 struct Layout {
     int m_total = 0, n_max = 0, kb_total = 0;
@@ -100,10 +103,15 @@ template <int D, int BLK>
 bool set_lds_ceilings() {
     const int search_lds_max = fp::kSearchStageBytes<D, BLK> + fp::kSearchRowHeader +
                                fp::kSearchHeads<BLK> * kMaxBlocksPerSeq * (int)sizeof(float) + fp::kSearchCandBytes;
-    bool ok = hipFuncSetAttribute(reinterpret_cast<const void *>(fp::search_kernel<D, BLK, false>),
+    const int search_lds_max2 = std::min(search_lds_max + fp::kSearchStageBytes<D, BLK>, kLdsPerWorkgroup);
+    bool ok = hipFuncSetAttribute(reinterpret_cast<const void *>(fp::search_kernel<D, BLK, false, 1>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, search_lds_max) == hipSuccess;
-    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void *>(fp::search_kernel<D, BLK, true>),
+    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void *>(fp::search_kernel<D, BLK, true, 1>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, search_lds_max) == hipSuccess;
+    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void *>(fp::search_kernel<D, BLK, false, 2>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, search_lds_max2) == hipSuccess;
+    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void *>(fp::search_kernel<D, BLK, true, 2>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, search_lds_max2) == hipSuccess;
     ok = ok && hipFuncSetAttribute(reinterpret_cast<const void *>(fp::attn_kernel<D, BLK, true>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, fp::kAttnLds<D, BLK>) == hipSuccess;
     ok = ok && hipFuncSetAttribute(reinterpret_cast<const void *>(fp::attn_kernel<D, BLK, false>),
@@ -335,14 +343,24 @@ static fp_status launch_search_d(fp_plan *p, const void *Q, const void *K, float
     const int nchunk = (p->g + fp::kSearchHeads<BLK> - 1) / fp::kSearchHeads<BLK>;
     const dim3 grid(p->m_total * p->hkv * nchunk);
     const uint16_t *q = static_cast<const uint16_t *>(Q);
-    if (sel != nullptr)
-        fp::search_kernel<D, BLK, true><<<grid, 256, p->search_lds, st>>>(q, kb_hi, kb_lo, kb_norm, p->d_rows_ranked, p->d_order,
-                                                                     p->m_total, p->n_max, p->n_pad, p->hq, p->hkv, p->g, nchunk,
-                                                                     eps, nullptr, *sel);
-    else
-        fp::search_kernel<D, BLK, false><<<grid, 256, p->search_lds, st>>>(q, kb_hi, kb_lo, kb_norm, p->d_rows_ranked, p->d_order,
-                                                                      p->m_total, p->n_max, p->n_pad, p->hq, p->hkv, p->g, nchunk,
-                                                                      eps, scores, fp::SelectArgs{});
+    // With no more workgroups than CUs and more than one tile of pooled keys, each workgroup gets a second group of four waves
+    // that takes every other tile: a CU with one wave per SIMD waits for most of a step.  Same results (pooling and search of a
+    // 2000-token chunk behind 64K tokens, 256 workgroups of 17 tiles: 53.0 -> 48.0 us; 512 new tokens 48.1 -> 45.7).
+    const size_t lds2 = p->search_lds + fp::kSearchStageBytes<D, BLK>;
+    const bool split = (int)grid.x <= kCus && p->n_max > 32 && lds2 <= (size_t)kLdsPerWorkgroup;
+    const auto launch = [&](auto select, auto groups) {
+        constexpr int NG = decltype(groups)::value;
+        fp::search_kernel<D, BLK, decltype(select)::value, NG><<<grid, 256 * NG, NG > 1 ? lds2 : p->search_lds, st>>>(
+            q, kb_hi, kb_lo, kb_norm, p->d_rows_ranked, p->d_order, p->m_total, p->n_max, p->n_pad, p->hq, p->hkv, p->g,
+            nchunk, eps, scores, sel != nullptr ? *sel : fp::SelectArgs{});
+    };
+    using std::integral_constant;
+    const auto launch_form = [&](auto select) {
+        if (split) launch(select, integral_constant<int, 2>{});
+        else launch(select, integral_constant<int, 1>{});
+    };
+    if (sel != nullptr) launch_form(integral_constant<bool, true>{});
+    else launch_form(integral_constant<bool, false>{});
     return launch_status();
 }
 }  // extern "C++"

@@ -119,7 +119,7 @@ template <int BLK> constexpr int kSearchHeads = 4 / kSearchWavesPerHead<BLK>;
 template <int BLK> constexpr int kSearchMailbox =
     2 * kSearchHeads<BLK> * (kSearchWavesPerHead<BLK> > 1 ? kSearchWavesPerHead<BLK> - 1 : 1) * 32 * 8;
 template <int D, int BLK> constexpr int kSearchStageBytes = kSearchBufs * kSearchTile<D> + kSearchMailbox<BLK>;
-constexpr int kSearchRowHeader = 64;                   // per-head row maxima and prologue exchange, ahead of the rows
+constexpr int kSearchRowHeader = 128;                  // per-group and head row maxima and prologue exchange, ahead of the rows
 constexpr int kSearchCandBytes = 4 * (32 + 4) * 4;     // SELECT: candidate tile indices + count per head
 constexpr float kSearchSafeLogit = 100.f;              // |x| below this: 2^x needs no reference point in fp32
 constexpr float kSearchEpsNoop = 0x1p-26f;             // eps below this cannot change an fp32 row total >= 1
@@ -231,8 +231,11 @@ struct SelectArgs {
     int32_t *idx, *cnt;
 };
 
-template <int D, int BLK, bool SELECT>
-__global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_kernel(
+// NG groups of four waves share a row, each with tile buffers and a mailbox of its own: group i takes tiles i, i + NG ..
+// A pair's t_J does not depend on who computes it.  What follows the loop is the first group's work (the scores' normalisation
+// everybody's).
+template <int D, int BLK, bool SELECT, int NG>
+__global__ __launch_bounds__(256 * NG, NG > 1 || D > 128 ? 2 : (SELECT ? 3 : 4)) void search_kernel(
     const uint16_t *__restrict__ Q, const uint16_t *__restrict__ kb_hi, const uint16_t *__restrict__ kb_lo,
     const float2 *__restrict__ kb_norm, const RowRec *__restrict__ rows_ranked, const int32_t *__restrict__ order,
     int m_total, int n_max, int n_pad, int hq, int hkv, int g, int nchunk, float eps, float *__restrict__ scores,
@@ -245,10 +248,10 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
     constexpr int WPH = kSearchWavesPerHead<BLK>;   // waves per query head
     constexpr int HPW = kSearchHeads<BLK>;          // query heads per workgroup
     constexpr int NPOST = WPH > 1 ? WPH - 1 : 1;    // mailbox slots per head and pooled key
-    float2 *mbox = reinterpret_cast<float2 *>(smem + kSearchBufs * kSearchTile<D>);
-    float *mtop = reinterpret_cast<float *>(smem + kSearchStageBytes<D, BLK>);   // [head] max of the row's pair maxima
-    float *xchg = mtop + 4;                                              // [wave] prologue exchange: query norm, key norm
+    float *mtop = reinterpret_cast<float *>(smem + NG * kSearchStageBytes<D, BLK>);   // [group][head] max of the row's pair maxima
+    float *xchg = mtop + 4 * NG;                                         // [wave] prologue exchange: query norm, key norm
     float *ms_all = mtop + kSearchRowHeader / sizeof(float);
+    static_assert(NG * (4 + 2 * 4) * sizeof(float) <= kSearchRowHeader, "row maxima and prologue exchange");
 
     const int per_row = hkv * nchunk;
     const int rank = blockIdx.x / per_row;
@@ -258,7 +261,10 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
     const RowRec bi = rows_ranked[rank];
     const int I = bi.I;
     const int tid = threadIdx.x, l = tid & 63, half = l >> 5;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, held in a scalar register
+    const int w_all = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, held in a scalar register
+    const int grp = NG > 1 ? w_all >> 2 : 0, w = NG > 1 ? w_all & 3 : w_all;   // group of four waves, wave within it
+    const uint32_t stage = NG > 1 ? (uint32_t)(grp * kSearchStageBytes<D, BLK>) : 0u;   // the group's tile buffers and mailbox
+    float2 *mbox = reinterpret_cast<float2 *>(smem + stage + kSearchBufs * kSearchTile<D>);
     const int hd = w / WPH, qh = w % WPH;   // head within the workgroup, 64-query part within the head
     const int hg = ch * HPW + hd;
     const bool active = hg < g;
@@ -278,7 +284,7 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
     }
     // Largest pooled-key norm of the row's causal blocks (for the bound on the logits).
     float kmax = 0.f;
-    for (int J = tid; J <= I; J += 256) kmax = fmaxf(kmax, knorm[(size_t)J * hkv].x);
+    for (int J = tid; J <= I; J += 256 * NG) kmax = fmaxf(kmax, knorm[(size_t)J * hkv].x);
 
     // Tile loads: D/8 wave-wide instructions per tile (2 planes x D/16 groups of 512/D rows), D/32
     // per wave (head dimension 128: 16 instructions, 4 per wave, 4 rows each).  Instruction
@@ -304,7 +310,7 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
 #define FP_LOAD_TILE(jt)                                                                                  \
     do {                                                                                                  \
         if (!hi_only || w < 2) {                                                                          \
-            const uint32_t dst_ = lds_base + (uint32_t)(((jt) % kSearchBufs) * kSearchTile<D>) + (w >> 1) * kSearchPlane<D>; \
+            const uint32_t dst_ = lds_base + FP_BUF(jt) + (w >> 1) * kSearchPlane<D>;                     \
             _Pragma("unroll") for (int i_ = 0; i_ < LPW; ++i_) {                                          \
                 int J_ = 32 * (jt) + ld_row[i_];                                                          \
                 J_ = J_ <= I ? J_ : I;                                                                    \
@@ -316,11 +322,11 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
     // B-fragment address inside a buffer: row l%32, chunk (2ks + half) ^ (row & kSwz) = 2ks ^ (half ^ (row & kSwz)).
     const int brow = l & 31;
     const uint32_t b_frag = (uint32_t)(brow * 2 * D + ((half ^ (brow & kSwz<D>)) << 4));
-#define FP_BUF(jt) ((uint32_t)(((jt) % kSearchBufs) * kSearchTile<D>))
+#define FP_BUF(jt) (stage + (uint32_t)(((jt) / NG % kSearchBufs) * kSearchTile<D>))
 
     // Prologue: tile 0 (and the older Q and norm loads) landed; the waves exchange their largest
     // query norm (per head) and pooled-key norm (per workgroup).
-    FP_LOAD_TILE(0);
+    if (grp < ntile) FP_LOAD_TILE(grp);
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
@@ -330,8 +336,8 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
         const float qn = sqrtf(search_qnorm2<D>(qa));
         kmax = wave_max(kmax);
         if (l == 0) {
-            xchg[2 * w] = qn;
-            xchg[2 * w + 1] = kmax;
+            xchg[2 * w_all] = qn;
+            xchg[2 * w_all + 1] = kmax;
         }
     }
     __syncthreads();
@@ -340,12 +346,15 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
 #pragma unroll
     for (int i = 1; i < WPH; ++i) qn_head = fmaxf(qn_head, xchg[2 * (hd * WPH + i)]);
     const float qnorm = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(qn_head)));   // all queries of the head's q-block
-    kmax = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(fmaxf(fmaxf(xchg[1], xchg[3]), fmaxf(xchg[5], xchg[7])))));
+    kmax = xchg[1];
+#pragma unroll
+    for (int i = 1; i < 4 * NG; ++i) kmax = fmaxf(kmax, xchg[2 * i + 1]);
+    kmax = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(kmax)));
     // small: no logit of this row can leave (-100, 100), and eps is a rounding no-op
     const bool small = !ragged && qnorm * kmax * 1.01f < kSearchSafeLogit && eps <= kSearchEpsNoop;
 
-    // Step jt: tile jt is complete in LDS.  Issue tile jt+1 into the other buffer (its readers,
-    // step jt-1's MFMAs, are behind the barrier), compute and reduce tile jt; the upper query half
+    // Step i (jt = i NG + group): tile jt is complete in LDS.  Issue the group's next tile into the other buffer (its readers,
+    // the previous step's MFMAs, are behind the barrier), compute and reduce tile jt; the upper query half
     // posts its (max, sum) in the mailbox, the lower half merges the previous tile's post with
     // its own pair from the previous step and files the result; wait for tile jt+1.
     float2 prev = make_float2(-INFINITY, 0.f);
@@ -367,20 +376,20 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
             m_top = fmaxf(m_top, mg_.x);                                                                  \
         }                                                                                                 \
     } while (0)
-#define FP_STEP(RAGGED, SMALL, BOTH, jt)                                                                  \
+#define FP_STEP(RAGGED, SMALL, BOTH, i_)                                                                  \
     do {                                                                                                  \
-        const int jt_ = (jt);                                                                             \
-        if (jt_ + 1 < ntile) FP_LOAD_TILE(jt_ + 1);                                                       \
-        if (active) {                                                                                     \
+        const int jt_ = (i_) * NG + grp;                                                                  \
+        if (jt_ + NG < ntile) FP_LOAD_TILE(jt_ + NG);                                                     \
+        if (active && (NG == 1 || jt_ < ntile)) {                                                         \
             f32x16 acc_[2];                                                                               \
             search_mma<D, BOTH>(smem, FP_BUF(jt_) + b_frag, qa, acc_);                                       \
             const float2 v_ = SMALL ? search_reduce_small(acc_) : search_reduce<RAGGED>(acc_, bi.q_len, 64 * qh, half); \
             if (l < 32) {                                                                                 \
                 if (qh) {                                                                                 \
-                    FP_MBOX(jt_ & 1, qh) = v_;                                                            \
+                    FP_MBOX((i_) & 1, qh) = v_;                                                           \
                 } else {                                                                                  \
-                    const int Jp_ = 32 * (jt_ - 1) + l;                                                   \
-                    if (jt_ > 0 && Jp_ <= I) FP_FILE(SMALL, Jp_, (jt_ - 1) & 1);                          \
+                    const int Jp_ = 32 * (jt_ - NG) + l;                                                  \
+                    if ((i_) > 0 && Jp_ <= I) FP_FILE(SMALL, Jp_, ((i_) - 1) & 1);                        \
                     prev = v_;                                                                            \
                 }                                                                                         \
             }                                                                                             \
@@ -389,27 +398,29 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
         __syncthreads();                                                                                  \
     } while (0)
 
+    const int nstep = (ntile + NG - 1) / NG;   // the same for every wave
     if (ragged) {
-        for (int jt = 0; jt < ntile; ++jt) FP_STEP(true, false, true, jt);
+        for (int i = 0; i < nstep; ++i) FP_STEP(true, false, true, i);
     } else if (hi_only) {
         if (small) {
-            for (int jt = 0; jt < ntile; ++jt) FP_STEP(false, true, false, jt);
+            for (int i = 0; i < nstep; ++i) FP_STEP(false, true, false, i);
         } else {
-            for (int jt = 0; jt < ntile; ++jt) FP_STEP(false, false, false, jt);
+            for (int i = 0; i < nstep; ++i) FP_STEP(false, false, false, i);
         }
     } else if (small) {
-        for (int jt = 0; jt < ntile; ++jt) FP_STEP(false, true, true, jt);
+        for (int i = 0; i < nstep; ++i) FP_STEP(false, true, true, i);
     } else {
-        for (int jt = 0; jt < ntile; ++jt) FP_STEP(false, false, true, jt);
+        for (int i = 0; i < nstep; ++i) FP_STEP(false, false, true, i);
     }
 #undef FP_STEP
-    // the last tile's merge (its post is behind the loop's final barrier), then everyone meets once
+    // the group's last tile's merge (its post is behind the loop's final barrier), then everyone meets once
     // more so that both waves of a head see the complete row
     if (active && qh == 0) {
-        const int Jp = 32 * (ntile - 1) + l;
-        if (l < 32 && Jp <= I) FP_FILE(small, Jp, (ntile - 1) & 1);
+        const int mine = (ntile - grp + NG - 1) / NG;   // the group's tiles
+        const int Jp = 32 * ((mine - 1) * NG + grp) + l;
+        if (l < 32 && mine > 0 && Jp <= I) FP_FILE(small, Jp, (mine - 1) & 1);
         m_top = wave_max(m_top);
-        if (l == 0) mtop[hd] = m_top;
+        if (l == 0) mtop[4 * grp + hd] = m_top;
     }
     __syncthreads();
 
@@ -438,7 +449,7 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
         constexpr int NB = 8;
         const int nchunks = I / 64 + 1;
         unsigned long long mine = 0ull;
-        if (active && qh == 0) {
+        if (active && qh == 0 && grp == 0) {
             for (int i0 = 0; i0 < nchunks; i0 += NB) {
                 float nl[NB];
 #pragma unroll
@@ -463,7 +474,7 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
         // interval that meets [T_lo, T_hi] + log2 alpha, every decision already has a margin against
         // any T in [T_lo, T_hi]: nothing is re-scored, not even the pairs that may hold the max, and
         // the row's approximate max stands in for T below.
-        if (active && qh == 0) {
+        if (active && qh == 0 && grp == 0) {
             bool hinge = false;
             float t_apx = -INFINITY;
             for (int i0 = 0; i0 < nchunks; i0 += NB) {
@@ -489,7 +500,7 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
             }
         }
         for (;;) {
-            if (qh == 0) {
+            if (qh == 0 && grp == 0) {
                 int have = 0, first = 0;
                 if (active) {
                     while (have < 32) {
@@ -513,7 +524,7 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
             const int32_t *cand0 = reinterpret_cast<int32_t *>(ms_all + (size_t)HPW * n_pad);
             const int n0 = cand0[32], n1 = cand0[36 + 32];
             if (n0 == 0 && n1 == 0) break;
-            const int nmine = hd ? n1 : n0;
+            const int nmine = grp ? 0 : (hd ? n1 : n0);   // the first group's waves re-score
             if (nmine > 0) {   // wave qh gathers plane qh of the head's tile: 2 LPW instructions of RPL rows
                 const char *pb = reinterpret_cast<const char *>(qh ? kb_lo : kb_hi) + pl_off;
                 const uint32_t dst = lds_base + (uint32_t)(hd * kSearchTile<D> + qh * kSearchPlane<D>);
@@ -557,7 +568,7 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
 #undef FP_FILE
 #undef FP_MBOX
     if (!active) return;
-    if (SELECT && qh) return;   // the list is compacted by one wave per head
+    if (SELECT && (qh || grp)) return;   // the list is compacted by one wave per head
     // Eq. 3-4.  With M the max of the row's pair maxima, S'_J = S_J 2^(m_J - M) and the score is
     // S'_J / (sum_K S'_K + eps).  The row holds t_J = m_J + log2 S_J (half the LDS of the pair), so
     // the same ratio is formed relative to T = max_J t_J: S'_J = 2^(t_J - T) * 2^(T - M), i.e.
@@ -572,10 +583,13 @@ __global__ __launch_bounds__(256, D > 128 ? 2 : (SELECT ? 3 : 4)) void search_ke
     float tot = 0.f;
     for (int J = l; J <= I; J += 64) tot += fast_exp2(ms[J] - Tm);
     tot = wave_sum(tot);
-    const float denom = tot + (small ? 0.f : eps * fast_exp2(mtop[hd] - Tm));
+    float M = mtop[hd];
+#pragma unroll
+    for (int i = 1; i < NG; ++i) M = fmaxf(M, mtop[4 * i + hd]);
+    const float denom = tot + (small ? 0.f : eps * fast_exp2(M - Tm));
     if (!SELECT) {   // the head's waves share the sequence's columns; columns past its last key block are left alone
         float *out = scores + ((size_t)h * m_total + r) * n_max;
-        for (int J = l + 64 * qh; J < bi.n_kb; J += 64 * WPH) out[J] = J <= I ? fast_exp2(ms[J] - Tm) / denom : 0.f;
+        for (int J = l + 64 * (qh + WPH * grp); J < bi.n_kb; J += 64 * WPH * NG) out[J] = J <= I ? fast_exp2(ms[J] - Tm) / denom : 0.f;
         return;
     }
     // Fused Alg. 2: the normalised scores (the same fp32 expression as above) replace the row in
