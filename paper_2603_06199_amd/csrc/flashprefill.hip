@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "fp_attn.hpp"
+#include "fp_attn_pair.hpp"
 #include "fp_device.hpp"
 #include "fp_search.hpp"
 
@@ -101,6 +102,13 @@ int search_heads_per_wg(int block) { return block == 64 ? 4 : block == 128 ? 2 :
 
 template <int D, int BLK>
 bool set_lds_ceilings() {
+    if constexpr (BLK == 128 && D <= 128) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(fp::attn_pair_kernel<D, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                fp::kPairLds<D>) != hipSuccess ||
+            hipFuncSetAttribute(reinterpret_cast<const void *>(fp::attn_pair_kernel<D, false>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                fp::kPairLds<D>) != hipSuccess)
+            return false;
+    }
     const int search_lds_max = fp::kSearchStageBytes<D, BLK> + fp::kSearchRowHeader +
                                fp::kSearchHeads<BLK> * kMaxBlocksPerSeq * (int)sizeof(float) + fp::kSearchCandBytes;
     const int search_lds_max2 = std::min(search_lds_max + fp::kSearchStageBytes<D, BLK>, kLdsPerWorkgroup);
@@ -452,6 +460,19 @@ static fp_status launch_attn_d(fp_plan *p, bool sparse, const void *Q, const voi
     const uint16_t *q = static_cast<const uint16_t *>(Q), *k = static_cast<const uint16_t *>(K),
                    *v = static_cast<const uint16_t *>(V);
     uint16_t *o = static_cast<uint16_t *>(O);
+    if constexpr (BLK == 128 && D <= 128) {
+        // q-blocks for half the CUs at most: two workgroups each, two waves per 32 queries (fp_attn_pair.hpp says why not beyond)
+        if (2 * n_super * p->g <= kCus) {
+            const dim3 pairs(2 * grid);   // two workgroups per q-block
+            if (sparse)
+                fp::attn_pair_kernel<D, true><<<pairs, 64 * fp::kPairWaves, fp::kPairLds<D>, st>>>(q, k, v, idx, cnt, p->d_rows_ranked, p->d_order, p->m_total,
+                                                                          p->n_max, p->hq, p->hkv, p->g, p->T, p->c, o, lse);
+            else
+                fp::attn_pair_kernel<D, false><<<pairs, 64 * fp::kPairWaves, fp::kPairLds<D>, st>>>(q, k, v, nullptr, nullptr, p->d_rows_ranked, p->d_order, p->m_total,
+                                                                          p->n_max, p->hq, p->hkv, p->g, p->T, p->c, o, lse);
+            return launch_status();
+        }
+    }
     if (sparse)
         fp::attn_kernel<D, BLK, true><<<dim3(grid), 64 * fp::kAttnWaves<BLK>, fp::kAttnLds<D, BLK>, st>>>(q, k, v, idx, cnt, p->d_rows_ranked, p->d_order, p->m_total,
                                                                           p->n_max, p->hq, p->hkv, p->g, p->T, p->c, o, lse);
