@@ -8,13 +8,15 @@ namespace fp {
 // LDS: two K buffers and two V buffers of one 64-key tile (64 rows x 2D bytes, unpadded) each.
 // Tiles are written by direct global->LDS loads (16 B per lane, lane i lands at base + 16 i), so
 // bank conflicts are avoided by permuting the 16-byte chunks inside a row instead of padding
-// (stated for head dimension 128, 16 chunks per row; the masks shrink with the row for 64, whose rows are half a turn
-// of the banks long: there K rows eight apart meet, and half of the LDS unit's active cycles are conflicts):
+// (stated for head dimension 128, 16 chunks per row; at 64 a row is half a turn of the banks long, so that two neighbouring
+// rows share a value and r/2 takes the place of r: with r itself rows eight apart met in K and two apart in V, and half of
+// the LDS unit's active cycles were conflicts; 16K tokens 274.7 -> 273.6 us, the vector work bounds it):
 //   K row r keeps chunk c at position c ^ (r & 15): the A-fragment reads of 16 consecutive rows
 //     at one chunk index then hit 16 different bank groups;
 //   V row r keeps chunk c at position c ^ 4 (r & 3): the four rows a transpose read touches per
 //     lane group then hit four different 64-byte bank groups.
-// Head dimension 128: 16 KB tiles, 64 KB, two workgroups per CU (registers).  64: 32 KB, three.
+// Head dimension 128: 16 KB tiles, 64 KB, two workgroups per CU (registers).  64: 32 KB, three (full attention, 16K tokens:
+// 1151 us with two, 1137 with three).
 // 256: 32 KB tiles, 128 KB, one workgroup (its accumulators and query fragments need 512 registers).
 // A workgroup has one wave per 32 queries of its q-block part, four at most; a 64-query block gets
 // two waves and 32-key tiles (32 KB, four workgroups per CU), so that every wave still loads 16
@@ -26,7 +28,7 @@ template <int D, int KT> constexpr int kAttnTile = KT * kAttnRowBytes<D>;   // 1
 constexpr int kAttnKBufs = 2, kAttnVBufs = 2;
 template <int D, int KT> constexpr int kAttnVBase = kAttnKBufs * kAttnTile<D, KT>;
 template <int D, int BLK> constexpr int kAttnLds = (kAttnKBufs + kAttnVBufs) * kAttnTile<D, kAttnTileKeys<BLK>>;   // 65536 at D = 128
-template <int D> constexpr int kAttnVSwz = (D / 32 - 1 < 3 ? D / 32 - 1 : 3);     // V rows: chunk ^ 4 (r & kAttnVSwz)
+template <int D> __device__ __forceinline__ constexpr int attn_vswz(int r) { return D < 128 ? (r >> 1) & 1 : r & 3; }   // V rows: chunk ^ 4 attn_vswz(r)
 
 // ds_read_b64_tr_b16: within each group of 16 lanes the 16 x 4 b16 values addressed by the
 // lanes (lane j supplies 4 consecutive b16) are exchanged so that lane i receives, in element e,
@@ -334,7 +336,7 @@ __device__ __forceinline__ void attn_step(const char *smem, uint32_t k1, uint32_
 }
 
 template <int D, int BLK, bool SPARSE>
-__global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_kernel(
+__global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : D < 128 ? 3 : 2) void attn_kernel(
     const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
     const int32_t *__restrict__ idx, const int32_t *__restrict__ cnt, const RowRec *__restrict__ rows_ranked,
     const int32_t *__restrict__ order, int m_total, int n_max, int hq, int hkv, int g, int T, float c,
@@ -442,8 +444,8 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
         const int row = ld_row + RPL * i, off_row = kAttnRowInOffset<D> ? row : ld_row;
-        ld_kcol[i] = (uint32_t)((ld_pos ^ (row & kSwz<D>)) * 16) + (uint32_t)off_row * row_bytes;
-        ld_vcol[i] = (uint32_t)((ld_pos ^ (4 * (row & kAttnVSwz<D>))) * 16) + (uint32_t)off_row * row_bytes;
+        ld_kcol[i] = (uint32_t)((ld_pos ^ swz<D>(row)) * 16) + (uint32_t)off_row * row_bytes;
+        ld_vcol[i] = (uint32_t)((ld_pos ^ (4 * attn_vswz<D>(row))) * 16) + (uint32_t)off_row * row_bytes;
     }
     // Clamped load of sub-tile sub_ of block blk_: every row is kept at or before the sequence's last token.
 #define FP_LOAD(Xb, col_, blk_, sub_, ldsoff_)                                                            \
@@ -479,18 +481,18 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
     float l_run = 0.f;         // this lane's share of the running row sum
 
     // Fragment addresses inside a buffer.  K: rows l%32 and 32 + l%32, chunk
-    // (2ks + half) ^ (row & kSwz) = 2ks ^ (half ^ (row & kSwz)); rows 32 apart share the permutation.
+    // (2ks + half) ^ swz(row) = 2ks ^ (half ^ swz(row)); rows 32 apart share the permutation.
     const int krow = l & 31;
-    const uint32_t k_frag = (uint32_t)(krow * RB + ((half ^ (krow & kSwz<D>)) << 4));
+    const uint32_t k_frag = (uint32_t)(krow * RB + ((half ^ swz<D>(krow)) << 4));
     // V transpose reads: row 32kt + 16j + 4half + e (+8), e = (l%16)/4 = row & 3; 8-byte unit at
-    // dims 32dt + 16gq + 4cc, i.e. chunk 4dt + 2gq + cc/2, stored at chunk ^ 4(e & kAttnVSwz)
-    // = 4(dt ^ (e & kAttnVSwz)) + ...
+    // dims 32dt + 16gq + 4cc, i.e. chunk 4dt + 2gq + cc/2, stored at chunk ^ 4 vswz(e)
+    // = 4(dt ^ vswz(e)) + ...
     uint32_t v_frag[NDT];
     {
         const int e = (l & 15) >> 2, gq = (l & 31) >> 4, cc = l & 3;
         const uint32_t vb = (uint32_t)((4 * half + e) * RB + (2 * gq + (cc >> 1)) * 16 + 8 * (cc & 1));
 #pragma unroll
-        for (int dt = 0; dt < NDT; ++dt) v_frag[dt] = vb + (uint32_t)((dt ^ (e & kAttnVSwz<D>)) * 64);
+        for (int dt = 0; dt < NDT; ++dt) v_frag[dt] = vb + (uint32_t)((dt ^ attn_vswz<D>(e)) * 64);
     }
     // Causal limit of tile t for this lane: on the diagonal block, key kk of the tile is in the
     // lane's future if kk > query - tile offset (and keys past a ragged end lie beyond every stored
@@ -608,7 +610,7 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
     // global store touch 64 different rows.  The wave's 32 x D output tile is therefore turned
     // through LDS (its own 32 rows of the K buffers: their last reader and their last incoming load
     // finished before the barrier of the last-but-one step) into 16-byte pieces, D/8 lanes per row.
-    // Chunk c of row q is kept at chunk c ^ (q & kSwz) so that neither side meets a bank conflict.
+    // Chunk c of row q is kept at chunk c ^ swz(q) so that neither side meets a bank conflict.
     const float l_tot = halves_sum(l_run);
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
     {
@@ -621,7 +623,7 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
                 bf16x4 o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = (__bf16)(acc[dt][4 * q4 + e] * inv);
-                *reinterpret_cast<bf16x4 *>(ob + qrow * RB + (((4 * dt + q4) ^ (qrow & kSwz<D>)) << 4) + 8 * half) = o;
+                *reinterpret_cast<bf16x4 *>(ob + qrow * RB + (((4 * dt + q4) ^ swz<D>(qrow)) << 4) + 8 * half) = o;
             }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -632,7 +634,7 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : 2) void attn_ke
             const int orow = RPL * i + l / LPR;
             const u32x4 v = *reinterpret_cast<const u32x4 *>(ob + orow * RB + (pc << 4));
             if (32 * w + orow < q_len)
-                *reinterpret_cast<u32x4 *>(O + ((size_t)(q_tok0 + 32 * w + orow) * hq + h) * D + ((pc ^ (orow & kSwz<D>)) << 3)) = v;
+                *reinterpret_cast<u32x4 *>(O + ((size_t)(q_tok0 + 32 * w + orow) * hq + h) * D + ((pc ^ swz<D>(orow)) << 3)) = v;
         }
     }
     if (q_local < q_len && lse != nullptr && half == 0)

@@ -216,8 +216,8 @@ __global__ __launch_bounds__(64 * kPairWaves, 2) void attn_pair_kernel(
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
         const int row = ld_row + RPL * i;
-        ld_kcol[i] = (uint32_t)((ld_pos ^ (row & kSwz<D>)) * 16) + (uint32_t)row * row_bytes;
-        ld_vcol[i] = (uint32_t)((ld_pos ^ (4 * (row & kAttnVSwz<D>))) * 16) + (uint32_t)row * row_bytes;
+        ld_kcol[i] = (uint32_t)((ld_pos ^ swz<D>(row)) * 16) + (uint32_t)row * row_bytes;
+        ld_vcol[i] = (uint32_t)((ld_pos ^ (4 * attn_vswz<D>(row))) * 16) + (uint32_t)row * row_bytes;
     }
     // clamped load: every row is kept at or before the sequence's last token (keys past the end are masked as future)
     const auto load_tail = [&](const char *Xb, const uint32_t (&col)[LPT], int blk, int sub_tile, uint32_t ldsoff) __attribute__((always_inline)) {
@@ -248,13 +248,13 @@ __global__ __launch_bounds__(64 * kPairWaves, 2) void attn_pair_kernel(
 
     // fragment addresses: attn_kernel's, K from this wave's 32 rows, V from its half of the dims
     const int krow = l & 31;
-    const uint32_t k_frag = (uint32_t)((32 * p + krow) * RB + ((half ^ (krow & kSwz<D>)) << 4));
+    const uint32_t k_frag = (uint32_t)((32 * p + krow) * RB + ((half ^ swz<D>(krow)) << 4));
     uint32_t v_frag[NDH];
     {
         const int e = (l & 15) >> 2, gq = (l & 31) >> 4, cc = l & 3;
         const uint32_t vb = (uint32_t)((4 * half + e) * RB + (2 * gq + (cc >> 1)) * 16 + 8 * (cc & 1));
 #pragma unroll
-        for (int i = 0; i < NDH; ++i) v_frag[i] = vb + (uint32_t)(((NDH * p + i) ^ (e & kAttnVSwz<D>)) * 64);
+        for (int i = 0; i < NDH; ++i) v_frag[i] = vb + (uint32_t)(((NDH * p + i) ^ attn_vswz<D>(e)) * 64);
     }
     const PairBufs xb = {smem + kPairXBase<D> + qw * kPairExchange + 16 * l, p, l};
     const auto lim_of = [&](int t) __attribute__((always_inline)) {   // causal limit for this lane's keys of tile t

@@ -17,10 +17,12 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // The kernels are templates over the head dimension D (64, 128 or 256).  A row of D bf16 is
-// D/8 16-byte chunks; LDS tiles are unpadded and keep chunk c of row r at position c ^ (r & kSwz<D>)
-// (see the kernels), where the mask is the row's chunk count minus one, capped at 15.
+// D/8 16-byte chunks; LDS tiles are unpadded and keep chunk c of row r at position c ^ swz<D>(r)
+// (see the kernels).
 template <int D> constexpr int kChunks = D / 8;                            // 16-byte chunks per row
-template <int D> constexpr int kSwz = (D / 8 < 16 ? D / 8 : 16) - 1;       // chunk permutation mask
+// Chunk permutation of row r: 16 consecutive rows at one chunk lie in 16 different bank groups of 16 bytes (the banks are 256
+// bytes wide: one row of D = 128, two of 64).
+template <int D> __device__ __forceinline__ constexpr int swz(int r) { return D < 128 ? (r >> 1) & (kChunks<D> - 1) : r & 15; }
 template <int D> constexpr int kRowsPerLoad = 512 / D;                     // rows one 1 KB wave-wide load covers
 constexpr float kLog2e = 1.4426950408889634f;
 

@@ -289,7 +289,7 @@ __global__ __launch_bounds__(256 * NG, NG > 1 || D > 128 ? 2 : (SELECT ? 3 : 4))
     // Tile loads: D/8 wave-wide instructions per tile (2 planes x D/16 groups of 512/D rows), D/32
     // per wave (head dimension 128: 16 instructions, 4 per wave, 4 rows each).  Instruction
     // q = LPW w + i covers plane q / (2 LPW), rows RPL (q % (2 LPW)) + l / LPR; lane l fills LDS
-    // position l % LPR of its row, i.e. fetches global chunk (l % LPR) ^ (row & kSwz).  Rows past the diagonal
+    // position l % LPR of its row, i.e. fetches global chunk (l % LPR) ^ swz(row).  Rows past the diagonal
     // (J > I) are clamped to I: they are computed and dropped.  A row that runs on the hi plane
     // alone does not load the other one (waves 2 and 3 then issue nothing).
     const int ntile = I / 32 + 1;
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(256 * NG, NG > 1 || D > 128 ? 2 : (SELECT ? 3 : 4))
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
         ld_row[i] = RPL * ((LPW * w + i) % (2 * LPW)) + l / LPR;
-        ld_col[i] = (uint32_t)(((l % LPR) ^ (ld_row[i] & kSwz<D>)) * 16);
+        ld_col[i] = (uint32_t)(((l % LPR) ^ swz<D>(ld_row[i])) * 16);
     }
 #define FP_LOAD_TILE(jt)                                                                                  \
     do {                                                                                                  \
@@ -319,9 +319,9 @@ __global__ __launch_bounds__(256 * NG, NG > 1 || D > 128 ? 2 : (SELECT ? 3 : 4))
         }                                                                                                 \
     } while (0)
 
-    // B-fragment address inside a buffer: row l%32, chunk (2ks + half) ^ (row & kSwz) = 2ks ^ (half ^ (row & kSwz)).
+    // B-fragment address inside a buffer: row l%32, chunk (2ks + half) ^ swz(row) = 2ks ^ (half ^ swz(row)).
     const int brow = l & 31;
-    const uint32_t b_frag = (uint32_t)(brow * 2 * D + ((half ^ (brow & kSwz<D>)) << 4));
+    const uint32_t b_frag = (uint32_t)(brow * 2 * D + ((half ^ swz<D>(brow)) << 4));
 #define FP_BUF(jt) (stage + (uint32_t)(((jt) / NG % kSearchBufs) * kSearchTile<D>))
 
     // Prologue: tile 0 (and the older Q and norm loads) landed; the waves exchange their largest
@@ -532,7 +532,7 @@ __global__ __launch_bounds__(256 * NG, NG > 1 || D > 128 ? 2 : (SELECT ? 3 : 4))
                 for (int i = 0; i < 2 * LPW; ++i) {
                     const int row = RPL * i + l / LPR;
                     const int J = cand[row];
-                    load_to_lds(pb, (uint32_t)J * row_bytes + (uint32_t)(((l % LPR) ^ (row & kSwz<D>)) * 16), dst + i * 1024);
+                    load_to_lds(pb, (uint32_t)J * row_bytes + (uint32_t)(((l % LPR) ^ swz<D>(row)) * 16), dst + i * 1024);
                 }
             }
             FP_WAIT_VMCNT(0);
