@@ -50,6 +50,7 @@ void *static_scratch(int device) {
 constexpr int kMaxBlocksPerSeq = 4096;
 constexpr int kLdsPerWorkgroup = 160 * 1024;
 constexpr int kCus = 256;
+constexpr size_t kKvCached = size_t(128) << 20;   // K and V that the last-level cache (256 MB) holds beside Q and O
 
 struct Layout {
     int m_total = 0, n_max = 0, kb_total = 0;
@@ -135,6 +136,7 @@ struct fp_plan {
     int head_dim = 0, block = 0;
     int m_total = 0, n_max = 0, kb_total = 0;
     float c = 0.f;                    // tau * log2(e)
+    size_t kv_bytes = 0;              // K and V
     fp::RowRec *d_rows = nullptr;     // [m_total]
     int32_t *d_order = nullptr;       // [m_total] rows, most causal key blocks first
     fp::RowRec *d_rows_ranked = nullptr;   // [m_total] d_rows permuted by d_order
@@ -254,6 +256,7 @@ fp_status fp_plan_create_in(const fp_shape *shape, int device, void *workspace, 
     const float tau = shape->scale > 0.f ? shape->scale : 1.0f / std::sqrt((float)shape->head_dim);
     p->c = tau * fp::kLog2e;
     p->n_pad = (L.n_max + 31) / 32 * 32;
+    p->kv_bytes = (size_t)(shape->cu_seqlens_k ? shape->cu_seqlens_k : shape->cu_seqlens)[shape->nseq] * shape->hkv * shape->head_dim * 4;
     p->search_lds = (size_t)search_stage_bytes(shape->head_dim, shape->block) + fp::kSearchRowHeader +
                     (size_t)search_heads_per_wg(shape->block) * p->n_pad * sizeof(float) + fp::kSearchCandBytes;
 
@@ -460,24 +463,25 @@ static fp_status launch_attn_d(fp_plan *p, bool sparse, const void *Q, const voi
     const uint16_t *q = static_cast<const uint16_t *>(Q), *k = static_cast<const uint16_t *>(K),
                    *v = static_cast<const uint16_t *>(V);
     uint16_t *o = static_cast<uint16_t *>(O);
+    const int by_head = (p->hkv < 8 ? 8 % p->hkv == 0 : p->hkv % 8 == 0) && p->kv_bytes <= kKvCached;   // see attn_item
     if constexpr (BLK == 128 && D <= 128) {
         // q-blocks for half the CUs at most: two workgroups each, two waves per 32 queries (fp_attn_pair.hpp says why not beyond)
         if (2 * n_super * p->g <= kCus) {
             const dim3 pairs(2 * grid);   // two workgroups per q-block
             if (sparse)
-                fp::attn_pair_kernel<D, true><<<pairs, 64 * fp::kPairWaves, fp::kPairLds<D>, st>>>(q, k, v, idx, cnt, p->d_rows_ranked, p->d_order, p->m_total,
+                fp::attn_pair_kernel<D, true><<<pairs, 64 * fp::kPairWaves, fp::kPairLds<D>, st>>>(q, k, v, idx, cnt, p->d_rows_ranked, p->d_order, by_head, p->m_total,
                                                                           p->n_max, p->hq, p->hkv, p->g, p->T, p->c, o, lse);
             else
-                fp::attn_pair_kernel<D, false><<<pairs, 64 * fp::kPairWaves, fp::kPairLds<D>, st>>>(q, k, v, nullptr, nullptr, p->d_rows_ranked, p->d_order, p->m_total,
+                fp::attn_pair_kernel<D, false><<<pairs, 64 * fp::kPairWaves, fp::kPairLds<D>, st>>>(q, k, v, nullptr, nullptr, p->d_rows_ranked, p->d_order, by_head, p->m_total,
                                                                           p->n_max, p->hq, p->hkv, p->g, p->T, p->c, o, lse);
             return launch_status();
         }
     }
     if (sparse)
-        fp::attn_kernel<D, BLK, true><<<dim3(grid), 64 * fp::kAttnWaves<BLK>, fp::kAttnLds<D, BLK>, st>>>(q, k, v, idx, cnt, p->d_rows_ranked, p->d_order, p->m_total,
+        fp::attn_kernel<D, BLK, true><<<dim3(grid), 64 * fp::kAttnWaves<BLK>, fp::kAttnLds<D, BLK>, st>>>(q, k, v, idx, cnt, p->d_rows_ranked, p->d_order, by_head, p->m_total,
                                                                           p->n_max, p->hq, p->hkv, p->g, p->T, p->c, o, lse);
     else
-        fp::attn_kernel<D, BLK, false><<<dim3(grid), 64 * fp::kAttnWaves<BLK>, fp::kAttnLds<D, BLK>, st>>>(q, k, v, nullptr, nullptr, p->d_rows_ranked, p->d_order,
+        fp::attn_kernel<D, BLK, false><<<dim3(grid), 64 * fp::kAttnWaves<BLK>, fp::kAttnLds<D, BLK>, st>>>(q, k, v, nullptr, nullptr, p->d_rows_ranked, p->d_order, by_head,
                                                                            p->m_total, p->n_max, p->hq, p->hkv, p->g, p->T, p->c, o, lse);
     return launch_status();
 }

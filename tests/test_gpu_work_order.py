@@ -1,0 +1,31 @@
+"""The attention kernel deals (KV head, row) pairs to the XCDs in an order that depends on the number of KV heads and rows.  Every pair
+is served, once and rightly, whatever the numbers: each KV head's outputs equal those of that head on its own, bit for bit."""
+import pytest
+
+from paper_2603_06199_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+# divisors and multiples of the eight XCDs, and numbers that are neither
+@pytest.mark.parametrize("hkv", (1, 2, 3, 4, 5, 6, 8, 12, 16, 24))
+# one row, fewer and more than the XCDs, ragged ends; a packed batch
+@pytest.mark.parametrize("lens", ((77,), (128 * 7,), (128 * 8 + 1,), (128 * 19, 300, 128 * 2)))
+def test_heads_alone_and_together(hkv, lens):
+    group = 2
+    cu = [0]
+    for n in lens:
+        cu.append(cu[-1] + n)
+    print(f"[case] hkv={hkv} lens={lens}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(hkv)
+    Q = torch.randn((cu[-1], group * hkv, 128), generator=gen, device="cuda").bfloat16()
+    K, V = (torch.randn((cu[-1], hkv, 128), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    O = torch.full_like(Q, float("nan"))
+    together, alone = B.Plan(cu, group * hkv, hkv), B.Plan(cu, group, 1)
+    O, lse = together.fp_dense_prefill(Q, K, V, O)
+    for h in range(hkv):
+        Oh, lh = alone.fp_dense_prefill(Q[:, group * h:group * (h + 1)].contiguous(), K[:, h:h + 1].contiguous(), V[:, h:h + 1].contiguous())
+        assert torch.equal(O[:, group * h:group * (h + 1)], Oh) and torch.equal(lse[group * h:group * (h + 1)], lh)
+    assert bool(torch.isfinite(O).all())
+    together.close(); alone.close()
