@@ -128,6 +128,18 @@ bool set_lds_ceilings() {
     return ok;
 }
 
+// Ceilings of the kernels that a plan's calls launch, to what the largest supported shape needs (they belong to the kernel, not to
+// the plan, and plans of different sizes are alive together).
+bool set_lds_ceilings(int head_dim, int block) {
+    const int thr_lds_max = fp::kThresholdWaves * kMaxBlocksPerSeq * (int)sizeof(float);
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(fp::threshold_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, thr_lds_max) != hipSuccess ||
+        hipFuncSetAttribute(reinterpret_cast<const void *>(fp::threshold_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, thr_lds_max) != hipSuccess)
+        return false;
+    if (head_dim == 64) return set_lds_ceilings<64, 128>();
+    if (head_dim == 256) return set_lds_ceilings<256, 128>();
+    return block == 64 ? set_lds_ceilings<128, 64>() : block == 128 ? set_lds_ceilings<128, 128>() : set_lds_ceilings<128, 256>();
+}
+
 }  // namespace
 
 struct fp_plan {
@@ -317,15 +329,7 @@ fp_status fp_plan_create_in(const fp_shape *shape, int device, void *workspace, 
     ok = ok && hipMemcpy(p->d_kblk, kblk.data(), kblk.size() * sizeof(fp::KeyBlockRec), hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && hipMemcpy(p->d_order, order.data(), order.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && hipMemcpy(p->d_rows_ranked, rows_ranked.data(), rows.size() * sizeof(fp::RowRec), hipMemcpyHostToDevice) == hipSuccess;
-    // The dynamic-LDS ceilings are per kernel, not per plan: they are set to what the largest
-    // supported shape needs, so that plans of different sizes can be alive together.
-    ok = ok && set_lds_ceilings<64, 128>() && set_lds_ceilings<128, 64>() && set_lds_ceilings<128, 128>() &&
-         set_lds_ceilings<128, 256>() && set_lds_ceilings<256, 128>();
-    const int thr_lds_max = fp::kThresholdWaves * kMaxBlocksPerSeq * (int)sizeof(float);
-    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void *>(fp::threshold_kernel<true>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, thr_lds_max) == hipSuccess;
-    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void *>(fp::threshold_kernel<false>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, thr_lds_max) == hipSuccess;
+    ok = ok && set_lds_ceilings(shape->head_dim, shape->block);
     (void)hipSetDevice(prev);
     if (!ok) {
         (void)hipGetLastError();
