@@ -14,8 +14,9 @@ namespace fp {
  * It is for launches that leave half the CUs idle, where the time is the longest row's chain of steps, and a step what one
  * wave per SIMD can issue: about 1700 cycles there (1024 of them matrix work), 1350 here.  Attention alone, both in turn on one
  * card, us: 4K tokens of 4 heads 28.3 -> 26.7 (whole pass 40.3 -> 38.1), 3000 tokens 23.3 -> 21.7, a 512-token chunk of 32 heads
- * behind 64K tokens 71.6 -> 67.6; rows of one or two blocks 0 to 1 us less.  With twice the q-blocks (1000 tokens of 32 heads,
- * two workgroups per CU) it was slower, 18.9 -> 23.3, and at head dimension 256, where the LDS is busiest, 517 -> 537.
+ * behind 64K tokens 71.6 -> 67.6; rows of one or two blocks 0 to 1 us less.  A form with two barriers a step that fitted a CU twice
+ * was slower with twice the q-blocks (1000 tokens of 32 heads: 18.9 -> 23.3) and at head dimension 256, where the LDS is
+ * busiest (517 -> 537).
  *
  * Every sum is formed from the same terms in the same order as there, and the reference point of the softmax moves on the same
  * tiles, so both kernels give the same bits: which of them runs may depend on the launch.
