@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libflashprefill.so")
 PROBE = os.path.join(HERE, "mfma_probe")     # stand-alone measurement aid (bench.py --mfma-probe), not part of the library
 SOURCES = ["flashprefill.hip"]
-HEADERS = ["fp_device.hpp", "fp_search.hpp", "fp_attn.hpp", "fp_attn_pair.hpp"]
+HEADERS = ["fp_device.hpp", "fp_search.hpp", "fp_order.hpp", "fp_attn.hpp", "fp_attn_pair.hpp"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

@@ -50,7 +50,6 @@ void *static_scratch(int device) {
 constexpr int kMaxBlocksPerSeq = 4096;
 constexpr int kLdsPerWorkgroup = 160 * 1024;
 constexpr int kCus = 256;
-constexpr size_t kKvCached = size_t(128) << 20;   // K and V that the last-level cache (256 MB) holds beside Q and O
 
 struct Layout {
     int m_total = 0, n_max = 0, kb_total = 0;
@@ -463,29 +462,30 @@ template <int D, int BLK>
 static fp_status launch_attn_d(fp_plan *p, bool sparse, const void *Q, const void *K, const void *V, const int32_t *idx,
                                const int32_t *cnt, void *O, float *lse, hipStream_t st) {
     const int n_super = p->m_total * p->hkv;
-    const int grid = (n_super + 7) / 8 * 8 * p->g * (BLK > 128 ? BLK / 128 : 1);   // a 256-query block takes two workgroups
+    constexpr int QS = BLK > 128 ? BLK / 128 : 1;   // a 256-query block takes two workgroups
+    const int item_order = fp::attn_order(sparse, QS, p->m_total, p->hkv, p->g, (long long)p->kv_bytes);
+    const int grid = fp::kXcds * fp::attn_turns(item_order, p->m_total, p->hkv) * p->g * QS;
     const uint16_t *q = static_cast<const uint16_t *>(Q), *k = static_cast<const uint16_t *>(K),
                    *v = static_cast<const uint16_t *>(V);
     uint16_t *o = static_cast<uint16_t *>(O);
-    const int by_head = (p->hkv < 8 ? 8 % p->hkv == 0 : p->hkv % 8 == 0) && p->kv_bytes <= kKvCached;   // see attn_item
     if constexpr (BLK == 128 && D <= 128) {
         // q-blocks for half the CUs at most: two workgroups each, two waves per 32 queries (fp_attn_pair.hpp says why not beyond)
         if (2 * n_super * p->g <= kCus) {
             const dim3 pairs(2 * grid);   // two workgroups per q-block
             if (sparse)
-                fp::attn_pair_kernel<D, true><<<pairs, 64 * fp::kPairWaves, fp::kPairLds<D>, st>>>(q, k, v, idx, cnt, p->d_rows_ranked, p->d_order, by_head, p->m_total,
+                fp::attn_pair_kernel<D, true><<<pairs, 64 * fp::kPairWaves, fp::kPairLds<D>, st>>>(q, k, v, idx, cnt, p->d_rows_ranked, p->d_order, item_order, p->m_total,
                                                                           p->n_max, p->hq, p->hkv, p->g, p->T, p->c, o, lse);
             else
-                fp::attn_pair_kernel<D, false><<<pairs, 64 * fp::kPairWaves, fp::kPairLds<D>, st>>>(q, k, v, nullptr, nullptr, p->d_rows_ranked, p->d_order, by_head, p->m_total,
+                fp::attn_pair_kernel<D, false><<<pairs, 64 * fp::kPairWaves, fp::kPairLds<D>, st>>>(q, k, v, nullptr, nullptr, p->d_rows_ranked, p->d_order, item_order, p->m_total,
                                                                           p->n_max, p->hq, p->hkv, p->g, p->T, p->c, o, lse);
             return launch_status();
         }
     }
     if (sparse)
-        fp::attn_kernel<D, BLK, true><<<dim3(grid), 64 * fp::kAttnWaves<BLK>, fp::kAttnLds<D, BLK>, st>>>(q, k, v, idx, cnt, p->d_rows_ranked, p->d_order, by_head, p->m_total,
+        fp::attn_kernel<D, BLK, true><<<dim3(grid), 64 * fp::kAttnWaves<BLK>, fp::kAttnLds<D, BLK>, st>>>(q, k, v, idx, cnt, p->d_rows_ranked, p->d_order, item_order, p->m_total,
                                                                           p->n_max, p->hq, p->hkv, p->g, p->T, p->c, o, lse);
     else
-        fp::attn_kernel<D, BLK, false><<<dim3(grid), 64 * fp::kAttnWaves<BLK>, fp::kAttnLds<D, BLK>, st>>>(q, k, v, nullptr, nullptr, p->d_rows_ranked, p->d_order, by_head,
+        fp::attn_kernel<D, BLK, false><<<dim3(grid), 64 * fp::kAttnWaves<BLK>, fp::kAttnLds<D, BLK>, st>>>(q, k, v, nullptr, nullptr, p->d_rows_ranked, p->d_order, item_order,
                                                                            p->m_total, p->n_max, p->hq, p->hkv, p->g, p->T, p->c, o, lse);
     return launch_status();
 }

@@ -2,6 +2,7 @@
 // template, full causal attention.  bf16 MFMA for both contractions, fp32 online softmax.
 #pragma once
 #include "fp_device.hpp"
+#include "fp_order.hpp"
 
 namespace fp {
 
@@ -329,45 +330,11 @@ __device__ __forceinline__ void attn_step(const char *smem, uint32_t k1, uint32_
     attn_new_max<NDT>(tm, c, m_run, l_run, acc);
 }
 
-// Work order: KV head and row rank of an XCD's `turn`-th super-item; false if there is none.  Consecutive workgroup ids land on
-// different XCDs, each with its own L2; rows are ranked heaviest (largest I) first.
-//
-// by_head: an XCD has a KV head of its own (or 8 / hkv XCDs share one, dealt its rows there and back; or it has hkv / 8), all
-// rows of it heaviest first, so that every XCD gets the same share of long and short rows, ends on short ones and keeps one head's
-// K and V in its L2.  All heads' K and V are in use at once, which is good as long as they fit the last-level cache with room
-// to spare.  Whole passes, without -> with: 4K tokens of 32/4 heads 92.8 -> 88.2 us, 8K 207.5 -> 201.0, 16K of 32/8 489.0 -> 469.4,
-// head dimension 64 at 16K 277.5 -> 271.8, packed 0.5K-30K 1771 -> 1757, 64K of 32/4 (128 MiB of K and V) 2986 -> 2947;
-// 64K of 32/8 (256 MiB) 2776 -> 2782, 128K of 32/4 (256 MiB) 7505 -> 7612.
-//
-// Otherwise, with more K and V than that or a number of KV heads that does not go with 8: the KV head outermost, its rows
-// dealt to the XCDs there and back (in one direction only, XCD 0 got the heaviest row of every eight: dense, 16K tokens, 5 % more than
-// the mean, 1926 -> 1862 us).  The eight XCDs then work on neighbouring rows of the same KV head, so that one head's K and V
-// (128 MiB each at 512K tokens) are what the last-level cache holds at a time, not every head's.
-__device__ __forceinline__ bool attn_item(int xcd, int turn, int m_total, int hkv, int by_head, int &hk, int &rank) {
-    if (by_head) {
-        if (hkv < 8) {
-            const int per = 8 / hkv, sub = xcd / hkv;   // XCDs per KV head, which of them
-            hk = xcd % hkv;
-            rank = turn * per + (turn & 1 ? per - 1 - sub : sub);
-        } else {
-            const int heads = hkv / 8;                  // KV heads per XCD
-            hk = xcd + 8 * (turn % heads);
-            rank = turn / heads;
-        }
-        return rank < m_total;
-    }
-    const int s = turn * 8 + (turn & 1 ? 7 - xcd : xcd);
-    if (s >= m_total * hkv) return false;
-    hk = s / m_total;
-    rank = s - hk * m_total;
-    return true;
-}
-
 template <int D, int BLK, bool SPARSE>
 __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : D < 128 ? 3 : 2) void attn_kernel(
     const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
     const int32_t *__restrict__ idx, const int32_t *__restrict__ cnt, const RowRec *__restrict__ rows_ranked,
-    const int32_t *__restrict__ order, int by_head, int m_total, int n_max, int hq, int hkv, int g, int T, float c,
+    const int32_t *__restrict__ order, int item_order, int m_total, int n_max, int hq, int hkv, int g, int T, float c,
     uint16_t *__restrict__ O, float *__restrict__ lse) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int KS = D / 16;            // k-slices of the QK^T contraction
@@ -385,7 +352,7 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : D < 128 ? 3 : 2
     const int sub = k0 % QS, k = k0 / QS;             // which 128 queries of the q-block
     const int hg = k % g;
     int hk, rank;
-    if (!attn_item(x, k / g, m_total, hkv, by_head, hk, rank)) return;
+    if (!attn_item<SPARSE>(item_order, x, k / g, m_total, hkv, hk, rank)) return;
     hk = __builtin_amdgcn_readfirstlane(hk);       // held in scalar registers
     rank = __builtin_amdgcn_readfirstlane(rank);
     const int r = order[rank];               // both tables are indexed by rank: one round trip

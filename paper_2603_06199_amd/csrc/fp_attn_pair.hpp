@@ -140,7 +140,7 @@ template <int D, bool SPARSE>
 __global__ __launch_bounds__(64 * kPairWaves, 2) void attn_pair_kernel(
     const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
     const int32_t *__restrict__ idx, const int32_t *__restrict__ cnt, const RowRec *__restrict__ rows_ranked,
-    const int32_t *__restrict__ order, int by_head, int m_total, int n_max, int hq, int hkv, int g, int T, float c,
+    const int32_t *__restrict__ order, int item_order, int m_total, int n_max, int hq, int hkv, int g, int T, float c,
     uint16_t *__restrict__ O, float *__restrict__ lse) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int BLK = 128, KT = 64, TPB = BLK / KT;
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(64 * kPairWaves, 2) void attn_pair_kernel(
     const int sub = k0 % QS, k = k0 / QS;
     const int hg = k % g;
     int hk, rank;
-    if (!attn_item(xcd, k / g, m_total, hkv, by_head, hk, rank)) return;
+    if (!attn_item<false>(item_order, xcd, k / g, m_total, hkv, hk, rank)) return;
     hk = __builtin_amdgcn_readfirstlane(hk);       // held in scalar registers
     rank = __builtin_amdgcn_readfirstlane(rank);
     const int r = order[rank];

@@ -1,0 +1,78 @@
+// Order in which an attention launch's work is dealt to the eight XCDs.  No device code in here: it compiles for the host too.
+#pragma once
+
+namespace fp {
+
+constexpr int kXcds = 8;
+constexpr int kOrderDealt = 0, kOrderByHead = 1, kOrderRounds = 2;
+
+// KV head and row rank of an XCD's `turn`-th super-item (KV head, row); false if there is none.  Consecutive workgroup ids land on
+// different XCDs, each with its own L2, and a workgroup stays on its XCD; rows are ranked heaviest (most causal blocks) first.
+//
+// Sparse lists may be several times as long for one KV head as for another, so that an XCD must not depend on which heads it
+// serves: in both orders for them an XCD gets an eighth of every head's rows, there and back (in one direction only, XCD 0 got the
+// heaviest row of every eight).
+//   dealt    the KV head outermost: the XCDs work on neighbouring rows of one head, whose K and V (128 MiB each at 512K tokens)
+//            are what the last-level cache holds at a time, not every head's.
+//   rounds   rounds of eight rows, one row of every KV head per XCD and round, each XCD starting at another head: the heaviest rows of
+//            all heads run first and the launch ends on light ones.
+// In full attention all heads have the same work:
+//   by head  an XCD has a KV head of its own (8 / hkv XCDs share one; or it has hkv / 8): one head's K and V are what its L2 sees.
+// ROUNDS: whether the kernel's launches can have that order.
+template <bool ROUNDS>
+__host__ __device__ inline bool attn_item(int order, int xcd, int turn, int m_total, int hkv, int &hk, int &rank) {
+    if (ROUNDS && order == kOrderRounds) {
+        const int round = turn / hkv, head = turn - round * hkv + xcd * hkv / kXcds;
+        hk = head < hkv ? head : head - hkv;
+        const int place = (xcd + hk) % kXcds;   // turned from head to head: a last round of fewer rows takes other XCDs for each
+        rank = kXcds * round + (round & 1 ? kXcds - 1 - place : place);
+        return rank < m_total;
+    }
+    if (order == kOrderByHead) {
+        if (hkv < kXcds) {
+            const int per = kXcds / hkv, sub = xcd / hkv;   // XCDs per KV head, which of them
+            hk = xcd % hkv;
+            rank = turn * per + (turn & 1 ? per - 1 - sub : sub);
+        } else {
+            const int heads = hkv / kXcds;                  // KV heads per XCD
+            hk = xcd + kXcds * (turn % heads);
+            rank = turn / heads;
+        }
+        return rank < m_total;
+    }
+    const int s = turn * kXcds + (turn & 1 ? kXcds - 1 - xcd : xcd);
+    hk = s / m_total;
+    rank = s - hk * m_total;
+    return hk < hkv;
+}
+
+constexpr long long kKvCached = 128ll << 20;   // bytes of K and V that the last-level cache (256 MB) holds beside Q and O
+constexpr int kOrderCus = 256, kRoundsParts = 64;
+
+// Order of a launch; `parts` is the number of workgroups per q-block.  Attention alone, us, repeated on the same inputs; "equal": all KV
+// heads keep the same share of their blocks, "one full": one of them keeps all (32/8: query and KV heads; all orders give the same bits).
+//
+// Beyond kKvCached the orders that have every head's K and V in use at once lose (by head: 128K tokens of 32/4 heads, 256 MiB, whole pass
+// 7505 -> 7612).
+// Full attention: by head (dealt -> by head: 8K of 32/4 491.9 -> 470.0, packed 0.5K-9K of 32/8 789.2 -> 744.3, 32K 7292 -> 7298).
+// Sparse, one workgroup per CU at most: the longest list sets the time, whichever XCD has it, and K and V of one head per XCD serve
+// best (by head against dealt: 4K of 4/2 equal 32.2 -> 31.7, one full 47.6 -> 44.8; 1000 tokens of 32/8 18.8 -> 18.7; rounds 19.3).
+// Sparse, up to 64 workgroups per query head: rounds, which let no heavy row start late (dealt -> rounds: 2K of 32/4 equal 47.2 -> 39.1,
+// 4K 92.9 -> 89.3 and one full 106.8 -> 103.4, 8K 230.8 -> 221.2 and 297.1 -> 286.8; block 64 4K of 32/8 81.9 -> 76.9; head dimension
+// 256 7K 315 -> 305).  Longer rows are balanced either way, and one head's K and V at a time serve better (10K of 32/8 one full
+// 356 -> 359, 16K equal 560 -> 578, block 64 6K 144 -> 160, block 256 14K 506 -> 543).
+// By head would be the fastest for heads that keep alike and is up to twice as slow for others (16K of 32/8, dealt -> by head: equal
+// 560 -> 535, one full 722 -> 1354; 8K of 32/4 231 -> 219, 297 -> 384).
+inline int attn_order(bool sparse, int parts, int m_total, int hkv, int g, long long kv_bytes) {
+    if (kv_bytes > kKvCached) return kOrderDealt;
+    if (!sparse || (long long)m_total * hkv * g * parts <= kOrderCus)
+        return (hkv < kXcds ? kXcds % hkv == 0 : hkv % kXcds == 0) ? kOrderByHead : kOrderDealt;   // where KV heads go evenly with the XCDs
+    return m_total * parts <= kRoundsParts ? kOrderRounds : kOrderDealt;
+}
+
+// Super-items per XCD, with those that do not exist.
+inline int attn_turns(int order, int m_total, int hkv) {
+    return order == kOrderRounds ? (m_total + kXcds - 1) / kXcds * hkv : (m_total * hkv + kXcds - 1) / kXcds;
+}
+
+}  // namespace fp
