@@ -622,10 +622,12 @@ __global__ __launch_bounds__(64 * kAttnWaves<BLK>, D > 128 ? 1 : D < 128 ? 3 : 2
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const int pc = l % LPR;
+        int lo = l;   // opaque, so that the row of each store is not computed ahead and carried through the loop: no register is left at
+        asm volatile("" : "+v"(lo));   // head dimension 64 (one was spilled: 8 bytes of scratch)
+        const int pc = lo % LPR;
 #pragma unroll
         for (int i = 0; i < 32 / RPL; ++i) {
-            const int orow = RPL * i + l / LPR;
+            const int orow = RPL * i + lo / LPR;
             const u32x4 v = *reinterpret_cast<const u32x4 *>(ob + orow * RB + (pc << 4));
             if (32 * w + orow < q_len)
                 *reinterpret_cast<u32x4 *>(O + ((size_t)(q_tok0 + 32 * w + orow) * hq + h) * D + ((pc ^ swz<D>(orow)) << 3)) = v;
