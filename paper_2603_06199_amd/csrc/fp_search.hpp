@@ -330,7 +330,7 @@ __global__ __launch_bounds__(256 * NG, NG > 1 || D > 128 ? 2 : (SELECT ? 3 : 4))
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(qa[qt][ks]));   // Q has landed before the loop
+        for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qa[qt][ks]));   // Q has landed before the loop
     FP_WAIT_VMCNT(0);
     {
         const float qn = sqrtf(search_qnorm2<D>(qa));
