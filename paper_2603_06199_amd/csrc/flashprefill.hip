@@ -45,9 +45,6 @@ void *static_scratch(int device) {
     return g_scratch_ptr[device];
 }
 
-// (m, S) of one row for 2 heads must fit the score kernel's LDS next to its tile buffers
-// (2 x 16 KB + 1 KB + 2 x 8 B x blocks <= 160 KB would allow more; 4096 blocks = 512K tokens)
-constexpr int kMaxBlocksPerSeq = 4096;
 constexpr int kLdsPerWorkgroup = 160 * 1024;
 constexpr int kCus = 256;
 
@@ -81,7 +78,7 @@ fp_status check_shape(const fp_shape *s, Layout *out) {
         if (prefix < 0) return FP_ERR_INVALID_ARG;
         if (prefix % s->block != 0) return FP_ERR_UNSUPPORTED;
         const int64_t nkb = (klen + s->block - 1) / s->block;
-        if (nkb > kMaxBlocksPerSeq) return FP_ERR_UNSUPPORTED;
+        if (nkb > fp::kMaxBlocksPerSeq) return FP_ERR_UNSUPPORTED;
         L.n_max = std::max<int>(L.n_max, (int)nkb);
         L.prefix_blocks[i] = (int32_t)(prefix / s->block);
         L.row_offset[i + 1] = L.row_offset[i] + (int32_t)((qlen + s->block - 1) / s->block);
@@ -110,7 +107,7 @@ bool set_lds_ceilings() {
             return false;
     }
     const int search_lds_max = fp::kSearchStageBytes<D, BLK> + fp::kSearchRowHeader +
-                               fp::kSearchHeads<BLK> * kMaxBlocksPerSeq * (int)sizeof(float) + fp::kSearchCandBytes;
+                               fp::kSearchHeads<BLK> * fp::kMaxBlocksPerSeq * (int)sizeof(float) + fp::kSearchCandBytes;
     const int search_lds_max2 = std::min(search_lds_max + fp::kSearchStageBytes<D, BLK>, kLdsPerWorkgroup);
     bool ok = hipFuncSetAttribute(reinterpret_cast<const void *>(fp::search_kernel<D, BLK, false, 1>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, search_lds_max) == hipSuccess;
@@ -130,7 +127,7 @@ bool set_lds_ceilings() {
 // Ceilings of the kernels that a plan's calls launch, to what the largest supported shape needs (they belong to the kernel, not to
 // the plan, and plans of different sizes are alive together).
 bool set_lds_ceilings(int head_dim, int block) {
-    const int thr_lds_max = fp::kThresholdWaves * kMaxBlocksPerSeq * (int)sizeof(float);
+    const int thr_lds_max = fp::kThresholdWaves * fp::kMaxBlocksPerSeq * (int)sizeof(float);
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(fp::threshold_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, thr_lds_max) != hipSuccess ||
         hipFuncSetAttribute(reinterpret_cast<const void *>(fp::threshold_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, thr_lds_max) != hipSuccess)
         return false;

@@ -24,6 +24,9 @@ template <int D> constexpr int kChunks = D / 8;                            // 16
 // bytes wide: one row of D = 128, two of 64).
 template <int D> __device__ __forceinline__ constexpr int swz(int r) { return D < 128 ? (r >> 1) & (kChunks<D> - 1) : r & 15; }
 template <int D> constexpr int kRowsPerLoad = 512 / D;                     // rows one 1 KB wave-wide load covers
+// Key blocks of a sequence (512K tokens in blocks of 128).  The search keeps one float per block and head of a row in LDS beside its
+// tile buffers, which would allow more, and its candidates as 64 bits per lane, which would not.
+constexpr int kMaxBlocksPerSeq = 4096;
 constexpr float kLog2e = 1.4426950408889634f;
 
 // One q-block row.  Queries: first token of the block (index into Q and O) and the number of

@@ -445,10 +445,12 @@ __global__ __launch_bounds__(256 * NG, NG > 1 || D > 128 ? 2 : (SELECT ? 3 : 4))
         const float qn = qnorm * 1.004f;
         const float slack = 0x1p-15f + 0x1p-18f * qnorm * kmax;
         // The scanning wave reads the norms eight chunks of 64 pairs at a time (one after another, every chunk was a round trip to
-        // memory of its own: 17000 of a workgroup's 62000 cycles at 528 key blocks; pooling and search of 128K tokens 762 -> 745 us).  A lane keeps which of its pairs are candidates, chunk i in bit i (at most 64 chunks: kMaxBlocksPerSeq).
+        // memory of its own: 17000 of a workgroup's 62000 cycles at 528 key blocks; pooling and search of 128K tokens 762 -> 745 us).  A
+        // lane keeps which of its pairs are candidates, chunk i in bit i.
         constexpr int NB = 8;
         const int nchunks = I / 64 + 1;
         unsigned long long mine = 0ull;
+        static_assert(kMaxBlocksPerSeq <= 64 * 8 * (int)sizeof(mine), "a bit for every chunk");
         if (active && qh == 0 && grp == 0) {
             for (int i0 = 0; i0 < nchunks; i0 += NB) {
                 float nl[NB];
