@@ -113,8 +113,12 @@ def _stream_ptr(stream) -> int:
     import torch
     if stream is not None:
         return stream.cuda_stream
-    # the current device's current stream, without the Stream object that torch.cuda.current_stream() builds around it
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    # the current device's current stream, without the Stream object that torch.cuda.current_stream() builds around it; the calls are
+    # private to torch, and a release without them takes the public way
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(device())
 
 
 def _dev_ptr(t, dtype, shape: tuple, name: str):
