@@ -25,13 +25,14 @@ HIPCC_FLAGS = [
 
 # The kernels carry inline assembly whose correctness leans on this compiler's register handling:
 #   - query loads whose results are first touched behind an explicit s_waitcnt;
-#   - a hand-placed s_nop before v_permlane32_swap;
+#   - a hand-placed s_nop before v_permlane32_swap and v_permlane16_swap;
 #   - exponentials (v_exp_f32) and, at head dimension 256, the S^T MFMAs, whose wait states stand in the same
 #     statements; the exponentials' reads of S^T, which the row max before them has waited for; at head dimension 256
 #     the row max's own reads, which the PV MFMAs or attn_settle hold back, and no register copy of S^T before them;
 #   - direct-to-LDS loads whose scalar base no vector instruction has just written.
-# tests/test_wait_states.py checks these in the assembly of every attention kernel (all but the s_nop); the GPU tests
-# were run with this toolchain, and a different one has to pass both again before its output is trusted.
+# tests/test_wait_states.py and tests/test_wait_states_pair.py check these in the assembly of the attention kernels,
+# tests/test_wait_states_swaps.py the swaps in that of every kernel; the GPU tests were run with this toolchain, and a
+# different one has to pass all of them again before its output is trusted.
 TESTED_HIPCC = "7.2"
 
 
