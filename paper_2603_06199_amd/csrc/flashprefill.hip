@@ -466,7 +466,7 @@ static fp_status launch_attn_d(fp_plan *p, bool sparse, const void *Q, const voi
                    *v = static_cast<const uint16_t *>(V);
     uint16_t *o = static_cast<uint16_t *>(O);
     if constexpr (BLK == 128 && D <= 128) {
-        // q-blocks for half the CUs at most: two workgroups each, two waves per 32 queries (fp_attn_pair.hpp says why not beyond)
+        // q-blocks for half the CUs at most: two workgroups each, two waves per 32 queries (fp_attn_pair.hpp has both sides)
         if (2 * n_super * p->g <= kCus) {
             const dim3 pairs(2 * grid);   // two workgroups per q-block
             if (sparse)

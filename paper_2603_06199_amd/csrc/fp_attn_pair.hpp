@@ -14,9 +14,13 @@ namespace fp {
  * It is for launches that leave half the CUs idle, where the time is the longest row's chain of steps, and a step what one
  * wave per SIMD can issue: about 1700 cycles there (1024 of them matrix work), 1350 here.  Attention alone, both in turn on one
  * card, us: 4K tokens of 4 heads 28.3 -> 26.7 (whole pass 40.3 -> 38.1), 3000 tokens 23.3 -> 21.7, a 512-token chunk of 32 heads
- * behind 64K tokens 71.6 -> 67.6; rows of one or two blocks 0 to 1 us less.  A form with two barriers a step that fitted a CU twice
- * was slower with twice the q-blocks (1000 tokens of 32 heads: 18.9 -> 23.3) and at head dimension 256, where the LDS is
- * busiest (517 -> 537).
+ * behind 64K tokens 71.6 -> 67.6; rows of one or two blocks 0 to 1 us less.
+ * The line is one workgroup per CU, 128 q-blocks.  Beyond it some CUs take two, and a launch whose rows are all long takes as long as
+ * those: 160 q-blocks of 32 heads behind 32K tokens, 20 % of the blocks kept, 115.1 -> 160.5 (128: 113.9 -> 107.7; full attention 387 ->
+ * 657, 128: 373 -> 370), at head dimension 64, where a CU holds two workgroups, 82.9 -> 90.4 (128: 83.3 -> 69.8).  Launches whose short
+ * rows leave room for the second workgroup would gain beyond it (prompts of 160 q-blocks, 4 heads 40.6 -> 37.0, 32 heads 13.7 -> 12.6;
+ * 192: 45.6 -> 41.4 and 15.2 -> 16.5), which the number of q-blocks alone does not tell.  At head dimension 256, where the LDS is
+ * busiest, a form with two barriers a step was slower (517 -> 537).
  *
  * Every sum is formed from the same terms in the same order as there, and the reference point of the softmax moves on the same
  * tiles, so both kernels give the same bits: which of them runs may depend on the launch.
