@@ -46,7 +46,6 @@ void *static_scratch(int device) {
 }
 
 constexpr int kLdsPerWorkgroup = 160 * 1024;
-constexpr int kCus = 256;
 
 struct Layout {
     int m_total = 0, n_max = 0, kb_total = 0;
@@ -354,11 +353,8 @@ static fp_status launch_search_d(fp_plan *p, const void *Q, const void *K, float
     const int nchunk = (p->g + fp::kSearchHeads<BLK> - 1) / fp::kSearchHeads<BLK>;
     const dim3 grid(p->m_total * p->hkv * nchunk);
     const uint16_t *q = static_cast<const uint16_t *>(Q);
-    // With no more workgroups than CUs and more than one tile of pooled keys, each workgroup gets a second group of four waves
-    // that takes every other tile: a CU with one wave per SIMD waits for most of a step.  Same results (pooling and search of a
-    // 2000-token chunk behind 64K tokens, 256 workgroups of 17 tiles: 53.0 -> 48.0 us; 512 new tokens 48.1 -> 45.7).
-    const size_t lds2 = p->search_lds + fp::kSearchStageBytes<D, BLK>;
-    const bool split = (int)grid.x <= kCus && p->n_max > 32 && lds2 <= (size_t)kLdsPerWorkgroup;
+    const size_t lds2 = p->search_lds + fp::kSearchStageBytes<D, BLK>;   // two groups of waves, same results
+    const bool split = fp::search_two_groups(D, BLK, sel != nullptr, (int)grid.x, p->n_max) && lds2 <= (size_t)kLdsPerWorkgroup;
     const auto launch = [&](auto select, auto groups) {
         constexpr int NG = decltype(groups)::value;
         fp::search_kernel<D, BLK, decltype(select)::value, NG><<<grid, 256 * NG, NG > 1 ? lds2 : p->search_lds, st>>>(
@@ -467,7 +463,7 @@ static fp_status launch_attn_d(fp_plan *p, bool sparse, const void *Q, const voi
     uint16_t *o = static_cast<uint16_t *>(O);
     if constexpr (BLK == 128 && D <= 128) {
         // q-blocks for half the CUs at most: two workgroups each, two waves per 32 queries (fp_attn_pair.hpp has both sides)
-        if (2 * n_super * p->g <= kCus) {
+        if (2 * n_super * p->g <= fp::kCus) {
             const dim3 pairs(2 * grid);   // two workgroups per q-block
             if (sparse)
                 fp::attn_pair_kernel<D, true><<<pairs, 64 * fp::kPairWaves, fp::kPairLds<D>, st>>>(q, k, v, idx, cnt, p->d_rows_ranked, p->d_order, item_order, p->m_total,

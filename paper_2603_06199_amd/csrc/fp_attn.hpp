@@ -11,7 +11,7 @@ namespace fp {
 // bank conflicts are avoided by permuting the 16-byte chunks inside a row instead of padding
 // (stated for head dimension 128, 16 chunks per row; at 64 a row is half a turn of the banks long, so that two neighbouring
 // rows share a value and r/2 takes the place of r: with r itself rows eight apart met in K and two apart in V, and half of
-// the LDS unit's active cycles were conflicts; 16K tokens 274.7 -> 273.6 us, the vector work bounds it):
+// the LDS unit's active cycles were conflicts; 16K tokens 274.7 -> 273.9 us, the vector work bounds it):
 //   K row r keeps chunk c at position c ^ (r & 15): the A-fragment reads of 16 consecutive rows
 //     at one chunk index then hit 16 different bank groups;
 //   V row r keeps chunk c at position c ^ 4 (r & 3): the four rows a transpose read touches per

@@ -102,7 +102,7 @@ template <int N> __device__ __forceinline__ float row_turn(float x) {
 // Over the whole wave, result in every lane: halves, rows, then turns by 8, 4, 2 and 1 inside a row.  After a turn by n all
 // values repeat every n lanes, so that the next one meets the lane an exchange l ^ n/2 would meet: the sums are those of a
 // butterfly, bit for bit.  All six stages stay in registers; through the LDS crossbar (__shfl_xor) each was a round
-// trip of its own, and a row of the search goes through up to nine such reductions one after another (pooling and one-pass
+// trip of its own, and a row of the search goes through up to eight such reductions one after another (pooling and one-pass
 // search, 8K tokens: 26.1 -> 23.2 us, a 2000-token chunk 54.5 -> 52.6, head dimension 64 at 16K 28.0 -> 26.1).
 __device__ __forceinline__ float wave_max(float v) {
     float a, b;

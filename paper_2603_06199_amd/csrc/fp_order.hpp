@@ -1,9 +1,10 @@
-// Order in which an attention launch's work is dealt to the eight XCDs.  No device code in here: it compiles for the host too.
+// Rules of the launches: the order in which attention work is dealt to the eight XCDs, and the groups of waves of the search.  No device
+// code in here: it compiles for the host too.
 #pragma once
 
 namespace fp {
 
-constexpr int kXcds = 8;
+constexpr int kXcds = 8, kCus = 256;
 constexpr int kOrderDealt = 0, kOrderByHead = 1, kOrderRounds = 2;
 
 // KV head and row rank of an XCD's `turn`-th super-item (KV head, row); false if there is none.  Consecutive workgroup ids land on
@@ -47,7 +48,7 @@ __host__ __device__ inline bool attn_item(int order, int xcd, int turn, int m_to
 }
 
 constexpr long long kKvCached = 128ll << 20;   // bytes of K and V that the last-level cache (256 MB) holds beside Q and O
-constexpr int kOrderCus = 256, kRoundsParts = 64;
+constexpr int kRoundsParts = 64;
 
 // Order of a launch; `parts` is the number of workgroups per q-block.  Attention alone, us, repeated on the same inputs; "equal": all KV
 // heads keep the same share of their blocks, "one full": one of them keeps all (32/8: query and KV heads; all orders give the same bits).
@@ -65,7 +66,7 @@ constexpr int kOrderCus = 256, kRoundsParts = 64;
 // 560 -> 535, one full 722 -> 1354; 8K of 32/4 231 -> 219, 297 -> 384).
 inline int attn_order(bool sparse, int parts, int m_total, int hkv, int g, long long kv_bytes) {
     if (kv_bytes > kKvCached) return kOrderDealt;
-    if (!sparse || (long long)m_total * hkv * g * parts <= kOrderCus)
+    if (!sparse || (long long)m_total * hkv * g * parts <= kCus)
         return (hkv < kXcds ? kXcds % hkv == 0 : hkv % kXcds == 0) ? kOrderByHead : kOrderDealt;   // where KV heads go evenly with the XCDs
     return m_total * parts <= kRoundsParts ? kOrderRounds : kOrderDealt;
 }
@@ -73,6 +74,20 @@ inline int attn_order(bool sparse, int parts, int m_total, int hkv, int g, long 
 // Super-items per XCD, with those that do not exist.
 inline int attn_turns(int order, int m_total, int hkv) {
     return order == kOrderRounds ? (m_total + kXcds - 1) / kXcds * hkv : (m_total * hkv + kXcds - 1) / kXcds;
+}
+
+// Whether each row of a search launch gets a second group of four waves, which takes every other tile of 32 pooled keys: with no more
+// workgroups than CUs there is one wave per SIMD otherwise, which waits for most of a step.  A second set of buffers and longer barriers
+// cost about 1 us, at head dimension 256 3 us, so that it pays from some length of the longest row on, earlier the less work a
+// tile is: time of two groups over that of one, pooling and search of 2 to 8 rows (scores | lists in one pass):
+//   head dimension 64    64-95 key blocks 1.02 | 1.02, 96-127 0.99 | 0.98, 256 0.94 | 0.99, 448 0.90 | 0.95
+//   128, block 128       64-95 1.09 | 1.06, 128 1.03 | 1.05, 224 0.98 | 1.02, 352 0.95 | 1.00, 448 0.94 | 0.99
+//   block 64, 256        64-95 1.08 | 1.08, 192 1.00 | 1.01, 224 0.97 to 0.99 | 0.98 to 0.99, 448 0.92 to 0.97 | 0.94 to 0.98
+//   head dimension 256   64-95 1.17 | 1.13, 224 1.04 | 1.04, 352 1.00 | 1.01, 416 0.99 | 1.00, 512 0.93 | 0.93 (12 rows)
+// (2000-token chunk behind 64K tokens, 528 key blocks, 256 workgroups: 53.0 -> 48.0 us.)
+inline bool search_two_groups(int head_dim, int block, bool lists, int workgroups, int n_max) {
+    const int from = head_dim < 128 ? 96 : head_dim > 128 ? 416 : lists && block == 128 ? 352 : 224;
+    return workgroups <= kCus && n_max >= from;
 }
 
 }  // namespace fp

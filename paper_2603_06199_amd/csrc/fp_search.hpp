@@ -324,7 +324,7 @@ __global__ __launch_bounds__(256 * NG, NG > 1 || D > 128 ? 2 : (SELECT ? 3 : 4))
     const uint32_t b_frag = (uint32_t)(brow * 2 * D + ((half ^ swz<D>(brow)) << 4));
 #define FP_BUF(jt) (stage + (uint32_t)(((jt) / NG % kSearchBufs) * kSearchTile<D>))
 
-    // Prologue: tile 0 (and the older Q and norm loads) landed; the waves exchange their largest
+    // Prologue: the group's first tile (and the older Q and norm loads) landed; the waves exchange their largest
     // query norm (per head) and pooled-key norm (per workgroup).
     if (grp < ntile) FP_LOAD_TILE(grp);
 #pragma unroll
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(256 * NG, NG > 1 || D > 128 ? 2 : (SELECT ? 3 : 4))
     // Step i (jt = i NG + group): tile jt is complete in LDS.  Issue the group's next tile into the other buffer (its readers,
     // the previous step's MFMAs, are behind the barrier), compute and reduce tile jt; the upper query half
     // posts its (max, sum) in the mailbox, the lower half merges the previous tile's post with
-    // its own pair from the previous step and files the result; wait for tile jt+1.
+    // its own pair from the previous step and files the result; wait for the group's next tile.
     float2 prev = make_float2(-INFINITY, 0.f);
     float m_top = -INFINITY;
     // slot of (step parity, posting wave qh >= 1) for this head and lane

@@ -1,4 +1,5 @@
-"""A launch of the search with few workgroups gives each row to two groups of waves.  The results do not depend on
+"""A launch of the search with few workgroups and long rows gives each row to two groups of waves (from 96 key blocks on at head
+dimension 64, 224 to 416 elsewhere).  The results do not depend on
 that: a chunk's rows (few workgroups) equal the same rows of a plain prefill (many), bit for bit, for the scores, and so do
 the one-pass lists."""
 import numpy as np
@@ -42,9 +43,17 @@ def test_chunk_equals_plain_search_bitwise(head_dim, block, blocks, last):
     whole.close(); chunk.close()
 
 
+# every form in two groups: an odd number of tiles, an even one with one block in the last, and the same one tile on
+@pytest.mark.parametrize("blocks", (416, 417, 448, 449))
+@pytest.mark.parametrize("head_dim,block", ((128, 128), (64, 128), (256, 128), (128, 64), (128, 256)))
+@pytest.mark.parametrize("last", ("full", "ragged"))
+def test_long_rows_bitwise(head_dim, block, blocks, last):
+    test_chunk_equals_plain_search_bitwise(head_dim, block, blocks, last)
+
+
 # even and odd numbers of tiles in the hi-plane pass, whose first group re-scores all of a row's pairs, 32 at a time, while the second
 # takes the barriers: key blocks that differ by little, alpha in the middle of their scores
-@pytest.mark.parametrize("blocks", (192, 600))
+@pytest.mark.parametrize("blocks", (192, 448, 600))
 @pytest.mark.parametrize("head_dim,block", ((128, 128), (64, 128), (256, 128), (128, 64), (128, 256)))
 def test_many_rescored_pairs(head_dim, block, blocks):
     hq, hkv, new = 32, 8, 3

@@ -15,6 +15,7 @@ SHIM = """
 #define __device__
 #include "fp_order.hpp"
 extern "C" int order_of(int sparse, int parts, int m, int hkv, int g, long long kv) { return fp::attn_order(sparse, parts, m, hkv, g, kv); }
+extern "C" int two_groups(int d, int block, int lists, int wg, int n_max) { return fp::search_two_groups(d, block, lists, wg, n_max); }
 extern "C" int turns_of(int order, int m, int hkv) { return fp::attn_turns(order, m, hkv); }
 extern "C" void items(int order, int m, int hkv, int *out) {   // [xcd][turn][2], -1 where there is none
     const int turns = fp::attn_turns(order, m, hkv);
@@ -89,3 +90,14 @@ def test_rule(lib):
         # a launch that the pair kernel takes (q-blocks for half the CUs at most) never asks for rounds
         assert all(lib.order_of(s, 1, m, hkv, g, small) != ROUNDS for s in (0, 1) for m in range(1, 128 // hq + 1))
         assert lib.order_of(1, 2, 32, hkv, 64 // hkv, small) == ROUNDS and lib.order_of(1, 2, 33, hkv, 64 // hkv, small) == DEALT
+
+
+# (head dimension, block, lists in one pass): the longest rows on which a second group of waves was measured to lose, the shortest on
+# which it gains
+@pytest.mark.parametrize("form,loses,gains", (((64, 128, 0), 80, 128), ((64, 128, 1), 80, 160), ((128, 128, 0), 160, 256), ((128, 128, 1), 320, 416),
+                                              ((128, 64, 0), 160, 256), ((128, 64, 1), 192, 256), ((128, 256, 0), 192, 288), ((128, 256, 1), 192, 288),
+                                              ((256, 128, 0), 320, 448), ((256, 128, 1), 384, 448)))
+def test_second_group_of_the_search(lib, form, loses, gains):
+    assert not any(lib.two_groups(*form, wg, n) for wg in (1, 100, 256) for n in range(1, loses + 1))
+    assert all(lib.two_groups(*form, wg, n) for wg in (1, 100, 256) for n in range(gains, 4097))
+    assert not any(lib.two_groups(*form, 257, n) for n in range(1, 4097))
