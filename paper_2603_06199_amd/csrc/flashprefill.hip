@@ -456,7 +456,7 @@ static fp_status launch_attn_d(fp_plan *p, bool sparse, const void *Q, const voi
                                const int32_t *cnt, void *O, float *lse, hipStream_t st) {
     const int n_super = p->m_total * p->hkv;
     constexpr int QS = BLK > 128 ? BLK / 128 : 1;   // a 256-query block takes two workgroups
-    const int item_order = fp::attn_order(sparse, QS, p->m_total, p->hkv, p->g, (long long)p->kv_bytes);
+    const int item_order = fp::attn_order(sparse, D, QS, p->m_total, p->hkv, p->g, (long long)p->kv_bytes);
     const int grid = fp::kXcds * fp::attn_turns(item_order, p->m_total, p->hkv) * p->g * QS;
     const uint16_t *q = static_cast<const uint16_t *>(Q), *k = static_cast<const uint16_t *>(K),
                    *v = static_cast<const uint16_t *>(V);

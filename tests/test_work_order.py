@@ -14,7 +14,7 @@ SHIM = """
 #define __host__
 #define __device__
 #include "fp_order.hpp"
-extern "C" int order_of(int sparse, int parts, int m, int hkv, int g, long long kv) { return fp::attn_order(sparse, parts, m, hkv, g, kv); }
+extern "C" int order_of(int sparse, int d, int parts, int m, int hkv, int g, long long kv) { return fp::attn_order(sparse, d, parts, m, hkv, g, kv); }
 extern "C" int two_groups(int d, int block, int lists, int wg, int n_max) { return fp::search_two_groups(d, block, lists, wg, n_max); }
 extern "C" int turns_of(int order, int m, int hkv) { return fp::attn_turns(order, m, hkv); }
 extern "C" void items(int order, int m, int hkv, int *out) {   // [xcd][turn][2], -1 where there is none
@@ -40,7 +40,7 @@ def lib(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", hip_build.CSRC, "-o", str(d / "shim.so"), str(d / "shim.cpp")],
                    check=True, capture_output=True)
     so = ctypes.CDLL(os.fspath(d / "shim.so"))
-    so.order_of.argtypes = [ctypes.c_int] * 5 + [ctypes.c_longlong]
+    so.order_of.argtypes = [ctypes.c_int] * 6 + [ctypes.c_longlong]
     return so
 
 
@@ -62,14 +62,15 @@ def test_every_item_once(lib, hkv):
 # Weights fall with the rank.  Of eight consecutive ranks of a head an XCD takes one, which weighs no more than the mean of the eight
 # before: over the whole head it gets at most its eighth and the heaviest row.  In the dealt order a head may begin within a turn:
 # one more row.
+@pytest.mark.parametrize("head_dim", (64, 128, 256))
 @pytest.mark.parametrize("hq,hkv", ((32, 1), (32, 2), (24, 3), (32, 4), (28, 4), (32, 8), (16, 16), (48, 24)))
-def test_share_of_every_head(lib, hq, hkv):
+def test_share_of_every_head(lib, hq, hkv, head_dim):
     g = hq // hkv
     for m in (9, 12, 31, 32, 64, 65, 128, 200, 512):
         for parts in (1, 2):
             if m * hq * parts <= 256:      # one workgroup per CU at most: no shares
                 continue
-            order = lib.order_of(1, parts, m, hkv, g, 512 * m * hkv)
+            order = lib.order_of(1, head_dim, parts, m, hkv, g, 512 * m * hkv)
             weight = np.arange(m, 0, -1)
             for x in _items(lib, order, m, hkv):
                 mine = np.zeros(hkv)
@@ -82,14 +83,15 @@ def test_rule(lib):
     small, large = 8 << 20, (128 << 20) + 1
     for hq, hkv in ((32, 4), (32, 8), (24, 3), (4, 1)):
         g = hq // hkv
-        for m in (1, 8, 9, 64, 65, 1000):
-            assert lib.order_of(0, 1, m, hkv, g, small) == (DEALT if hkv == 3 else BY_HEAD)   # full attention: heads are alike
-            assert lib.order_of(0, 1, m, hkv, g, large) == lib.order_of(1, 1, m, hkv, g, large) == DEALT
-            want = (DEALT if hkv == 3 else BY_HEAD) if m * hq <= 256 else ROUNDS if m <= 64 else DEALT
-            assert lib.order_of(1, 1, m, hkv, g, small) == want
+        for d, most in ((64, 96), (128, 64), (256, 64)):
+            for m in (1, 8, 9, 64, 65, 96, 97, 1000):
+                assert lib.order_of(0, d, 1, m, hkv, g, small) == (DEALT if hkv == 3 else BY_HEAD)   # full attention: heads are alike
+                assert lib.order_of(0, d, 1, m, hkv, g, large) == lib.order_of(1, d, 1, m, hkv, g, large) == DEALT
+                want = (DEALT if hkv == 3 else BY_HEAD) if m * hq <= 256 else ROUNDS if m <= most else DEALT
+                assert lib.order_of(1, d, 1, m, hkv, g, small) == want
         # a launch that the pair kernel takes (q-blocks for half the CUs at most) never asks for rounds
-        assert all(lib.order_of(s, 1, m, hkv, g, small) != ROUNDS for s in (0, 1) for m in range(1, 128 // hq + 1))
-        assert lib.order_of(1, 2, 32, hkv, 64 // hkv, small) == ROUNDS and lib.order_of(1, 2, 33, hkv, 64 // hkv, small) == DEALT
+        assert all(lib.order_of(s, d, 1, m, hkv, g, small) != ROUNDS for s in (0, 1) for d in (64, 128) for m in range(1, 128 // hq + 1))
+        assert lib.order_of(1, 128, 2, 32, hkv, 64 // hkv, small) == ROUNDS and lib.order_of(1, 128, 2, 33, hkv, 64 // hkv, small) == DEALT
 
 
 # (head dimension, block, lists in one pass): the longest rows on which a second group of waves was measured to lose, the shortest on
