@@ -269,7 +269,7 @@ __device__ __forceinline__ float attn_tile_sum(const float (&ls)[KT / 32]) {
  * on one card, us): head dimension 256, 16K tokens 654 -> 561, dense 8K 633 -> 547; 128: 4K tokens of 4 heads 35.3 -> 30.4,
  * 32K tokens 1425 -> 1357, dense 32K 7992 -> 7801; 64: 16K tokens 275 -> 268; block 64: 32K tokens 1047 -> 997; block 256:
  * 1994 -> 1897.  Long rows at head dimension 128 gain least because the clock sets most of their rate: on all-zero inputs
- * the same launch of dense 32K takes 1 / 1.72 of the time (64: 1 / 1.49, 256: 1 / 1.41, 16K tokens).
+ * the same launch of dense 32K takes 1 / 1.71 of the time (64: 1 / 1.51, 256: 1 / 1.45, 16K tokens).
  */
 constexpr int kAttnRing = 4;
 enum { MAIN = 0, TAIL = 1, PEN = 2 };   // see the kernel

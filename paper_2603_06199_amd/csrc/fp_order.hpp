@@ -22,13 +22,6 @@ constexpr int kOrderDealt = 0, kOrderByHead = 1, kOrderRounds = 2;
 // ROUNDS: whether the kernel's launches can have that order.
 template <bool ROUNDS>
 __host__ __device__ inline bool attn_item(int order, int xcd, int turn, int m_total, int hkv, int &hk, int &rank) {
-    if (ROUNDS && order == kOrderRounds) {
-        const int round = turn / hkv, head = turn - round * hkv + xcd * hkv / kXcds;
-        hk = head < hkv ? head : head - hkv;
-        const int place = (xcd + hk) % kXcds;   // turned from head to head: a last round of fewer rows takes other XCDs for each
-        rank = kXcds * round + (round & 1 ? kXcds - 1 - place : place);
-        return rank < m_total;
-    }
     if (order == kOrderByHead) {
         if (hkv < kXcds) {
             const int per = kXcds / hkv, sub = xcd / hkv;   // XCDs per KV head, which of them
@@ -39,6 +32,13 @@ __host__ __device__ inline bool attn_item(int order, int xcd, int turn, int m_to
             hk = xcd + kXcds * (turn % heads);
             rank = turn / heads;
         }
+        return rank < m_total;
+    }
+    if (ROUNDS && order == kOrderRounds) {
+        const int round = turn / hkv, head = turn - round * hkv + xcd * hkv / kXcds;
+        hk = head < hkv ? head : head - hkv;
+        const int place = (xcd + hk) % kXcds;   // turned from head to head: a last round of fewer rows takes other XCDs for each
+        rank = kXcds * round + (round & 1 ? kXcds - 1 - place : place);
         return rank < m_total;
     }
     const int s = turn * kXcds + (turn & 1 ? kXcds - 1 - xcd : xcd);
