@@ -31,7 +31,7 @@ HIPCC_FLAGS = [
 #     the row max's own reads, which the PV MFMAs or attn_settle hold back, and no register copy of S^T before them;
 #   - direct-to-LDS loads whose scalar base no vector instruction has just written.
 # tests/test_wait_states.py and tests/test_wait_states_pair.py check these in the assembly of the attention kernels,
-# tests/test_wait_states_swaps.py the swaps in that of every kernel; the GPU tests were run with this toolchain, and a
+# tests/test_assembly_rules.py the swaps in that of every kernel; the GPU tests were run with this toolchain, and a
 # different one has to pass all of them again before its output is trusted.
 TESTED_HIPCC = "7.2"
 
