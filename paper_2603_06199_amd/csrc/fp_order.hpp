@@ -37,7 +37,8 @@ __host__ __device__ inline bool attn_item(int order, int xcd, int turn, int m_to
     if (ROUNDS && order == kOrderRounds) {
         const int round = turn / hkv, head = turn - round * hkv + xcd * hkv / kXcds;
         hk = head < hkv ? head : head - hkv;
-        const int place = (xcd + hk) % kXcds;   // turned from head to head: a last round of fewer rows takes other XCDs for each
+        // turned from head to head, once round over all of them: a last round of fewer rows takes other XCDs for each
+        const int place = (xcd + hk * kXcds / hkv) % kXcds;
         rank = kXcds * round + (round & 1 ? kXcds - 1 - place : place);
         return rank < m_total;
     }

@@ -59,6 +59,14 @@ def test_every_item_once(lib, hkv):
             assert got == [(h, r) for h in range(hkv) for r in range(m)], (order, m)
 
 
+# a last round of fewer than eight rows falls to other XCDs for each head
+@pytest.mark.parametrize("hkv", (1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 16, 24, 32))
+def test_items_per_xcd(lib, hkv):
+    for m in range(1, 70):
+        for order in (DEALT, ROUNDS):
+            assert max(len(x) for x in _items(lib, order, m, hkv)) <= -(-m * hkv // 8), (order, m)
+
+
 # Weights fall with the rank.  Of eight consecutive ranks of a head an XCD takes one, which weighs no more than the mean of the eight
 # before: over the whole head it gets at most its eighth and the heaviest row.  In the dealt order a head may begin within a turn:
 # one more row.
