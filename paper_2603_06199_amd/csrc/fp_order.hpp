@@ -57,15 +57,16 @@ constexpr long long kKvCached = 128ll << 20;   // bytes of K and V that the last
 // 7505 -> 7612).
 // Full attention: by head (dealt -> by head: 8K of 32/4 491.9 -> 470.0, packed 0.5K-9K of 32/8 789.2 -> 744.3, 32K 7292 -> 7298).
 // Sparse, one workgroup per CU at most: the longest list sets the time, whichever XCD has it, and K and V of one head per XCD serve
-// best (by head against dealt: 4K of 4/2 equal 32.2 -> 31.7, one full 47.6 -> 44.8; 1000 tokens of 32/8 18.8 -> 18.7; rounds 19.3).
+// best (dealt -> by head: 4K of 4/2 equal 31.9 -> 31.6, one full 47.2 -> 44.6; 1000 tokens of 32/8 17.9 -> 18.3, rounds 19.3).
 // Sparse, up to 64 workgroups per query head, 96 at head dimension 64, where a CU holds three for two: rounds, which let no heavy row
-// start late (dealt -> rounds: 2K of 32/4 equal 47.2 -> 39.1, 4K 92.9 -> 89.3 and one full 106.8 -> 103.4, 8K 230.8 -> 221.2 and
-// 297.1 -> 286.8; block 64 4K of 32/8 81.9 -> 76.9; head dimension 256 7K 315 -> 305; 64 9K of 32/8 167.8 -> 157.3 and 195.2 -> 195.1, 12K
-// of 16/2 128 -> 118 and 282 -> 237).  Longer rows are balanced either way, and one head's K and V at a time serve better (10K of 32/8
-// one full 356 -> 359, 16K equal 560 -> 578, block 64 6K 144 -> 160, block 256 14K 506 -> 543, head dimension 64 16K of 32/4 315 -> 327,
-// of 16/16 one full 256 -> 297).
+// start late (dealt -> rounds, equal and one full: 2K of 32/4 42.5 -> 38.6 and 44.4 -> 39.0, 4K 94.0 -> 91.3 and 108.9 -> 104.5, 8K
+// 236.2 -> 227.6 and 303.0 -> 297.2, of 32/8 241.1 -> 232.4 and 275.0 -> 271.3; block 64 4K of 32/8 82.9 -> 77.1 and 102.0 -> 97.8;
+// block 256 3K of 32/4 79.2 -> 74.8 and 82.0 -> 76.8; head dimension 256 7K of 32/8 372.3 -> 371.9 and 411.4 -> 413.0, on lists of real
+// density 315 -> 305; 64 9K of 32/8 173.6 -> 163.7 and 200.3 -> 206.6, 12K of 16/2 134.6 -> 121.2 and 285.2 -> 247.4).  Longer rows are
+// balanced either way, and one head's K and V at a time serve better (10K of 32/8 one full 356 -> 359, 16K equal 560 -> 578, block 64 6K
+// 144 -> 160, block 256 14K 506 -> 543, head dimension 64 16K of 32/4 315 -> 327, of 16/16 one full 256 -> 297).
 // By head would be the fastest for heads that keep alike and is up to twice as slow for others (16K of 32/8, dealt -> by head: equal
-// 560 -> 535, one full 722 -> 1354; 8K of 32/4 231 -> 219, 297 -> 384).
+// 576 -> 560, one full 743 -> 1361; 8K of 32/4 236 -> 219, 303 -> 383).
 inline int attn_order(bool sparse, int head_dim, int parts, int m_total, int hkv, int g, long long kv_bytes) {
     if (kv_bytes > kKvCached) return kOrderDealt;
     if (!sparse || (long long)m_total * hkv * g * parts <= kCus)
